@@ -467,7 +467,7 @@ void build_pipeline_args(plse_instance *h, int p, uint64_t seed) {
     uint8_t *S_new = S_all + (size_t)p * st;
     int32_t *f_all = at<int32_t>(h, L.f_all);
     const uint32_t slo = (uint32_t)seed, shi = (uint32_t)(seed >> 32);
-    A.init = InitArgs{dev_instance(h), S_all, f_all, p, next_pow2(std::max(4, h->nv)), slo, shi};
+    A.init = InitArgs{dev_instance(h), S_all, f_all, p, init_log2_buckets(h->nv), slo, shi};
     A.pop = PopSetupArgs{p, st, at<uint64_t>(h, L.uid), at<int32_t>(h, L.hc), S_all,
                          at<uint8_t>(h, L.S_off)};
     A.fill = FillArgs{at<uint32_t>(h, L.tabu), (size_t)p * h->nv * h->ts};
@@ -769,7 +769,7 @@ int admit(const std::vector<plse_instance *> &hs, int p, const uint64_t *seeds, 
     RC_TRY(launch_ctl(hs, true, s));
     size_t init_lds = 0;
     for (plse_instance *h : hs)
-        init_lds = std::max(init_lds, init_lds_bytes(dev_instance(h), next_pow2(std::max(4, h->nv))));
+        init_lds = std::max(init_lds, init_lds_bytes(dev_instance(h)));
     RC_TRY(launch_over(hs, &ArgBlock::init,
                        [&](const ArgList &L, int c) { return launch_init(L, c, p, init_lds, s); }));
     RC_TRY(launch_over(hs, &ArgBlock::pop,
@@ -1739,11 +1739,11 @@ int plse_stage_init(plse_handle h, int32_t p, uint64_t seed, void *stream, uint8
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     RC_TRY(stage_prepare(h, p, s));
-    h->args.init = InitArgs{dev_instance(h), S, f, p, next_pow2(std::max(4, h->nv)),
+    h->args.init = InitArgs{dev_instance(h), S, f, p, init_log2_buckets(h->nv),
                             (uint32_t)seed, (uint32_t)(seed >> 32)};
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_init(single(h, &ArgBlock::init), 1, p,
-                        init_lds_bytes(h->args.init.I, h->args.init.pow2), s));
+                        init_lds_bytes(h->args.init.I), s));
     return PLSE_OK;
 }
 
@@ -1782,11 +1782,11 @@ int autotune(plse_instance *h, int32_t sample, int32_t depth, uint64_t seed, hip
     uint8_t *S_in = at<uint8_t>(h, h->L.S_off), *S_out = at<uint8_t>(h, h->L.S_tmp);
     int32_t *f = at<int32_t>(h, h->L.f_tmp);
     uint64_t *cnt = at<uint64_t>(h, h->L.cnt);
-    h->args.init = InitArgs{dev_instance(h), S_in, f, sample, next_pow2(std::max(4, h->nv)),
+    h->args.init = InitArgs{dev_instance(h), S_in, f, sample, init_log2_buckets(h->nv),
                             (uint32_t)seed, (uint32_t)(seed >> 32)};
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_init(single(h, &ArgBlock::init), 1, sample,
-                        init_lds_bytes(h->args.init.I, h->args.init.pow2), s));
+                        init_lds_bytes(h->args.init.I), s));
     // phase-1 searches of `depth` iterations per shape; without `waves` the
     // waves per block stay with the handle's setting (or the occupancy
     // rule, which also weighs the uneven search lengths of later generations)

@@ -71,7 +71,7 @@ struct InitArgs {
     uint8_t *S;            // [p][stride] out
     int32_t *f;            // [p] out
     int32_t p;
-    int32_t pow2;          // power of two >= nv (sort size)
+    int32_t log2_buckets;  // buckets of the vertex order's counting sort
     uint32_t seed_lo, seed_hi;
 };
 
@@ -199,7 +199,8 @@ hipError_t launch_plits_persistent(const ArgList &L, int count, int p, int lds_p
                                    int slots_per_lane, int waves_per_block, bool partial,
                                    int blocks, uint32_t *queue, hipStream_t stream);
 hipError_t launch_init(const ArgList &L, int count, int p, size_t lds, hipStream_t stream);
-size_t init_lds_bytes(const DevInstance &I, int pow2);
+int init_log2_buckets(int nv);
+size_t init_lds_bytes(const DevInstance &I);
 hipError_t init_set_lds_limit(int bytes);
 hipError_t launch_best(const ArgList &L, int count, hipStream_t stream);
 hipError_t launch_pack(const ArgList &L, int count, size_t max_threads, hipStream_t stream);

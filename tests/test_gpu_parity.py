@@ -820,3 +820,21 @@ def test_generation_stages_full_size(torch_cuda, oracle_mod):
     out = s.stage_aux(torch.from_numpy(S[:p]).cuda(), partner, dpart, 2, 77)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(_np(out)[:, :I.nv], oracle_mod.aux(77, 2, S[:p, :I.nv], po, do))
+
+
+# --- initial population: every width of the colour masks, batches of 64 and remainders ------
+@pytest.mark.parametrize("n,ratio,p", [(1, 0.0, 3), (2, 0.0, 5), (8, 0.0, 2), (9, 0.1, 7),
+                                       (31, 0.3, 4), (32, 0.0, 4), (63, 0.5, 3), (64, 0.6, 3),
+                                       (100, 0.9, 2), (127, 0.0, 2), (10, 1.0, 2)])
+def test_init_orders(torch_cuda, oracle_mod, n, ratio, p):
+    """Orders at the edges of the one-, two- and four-word colour masks (31/32,
+    63/64, 127), and vertex counts of none, one, 64, and with remainders."""
+    g = gen.planted(n, ratio, n) if ratio else np.zeros((n, n), dtype=np.int8)
+    _say(f"init n={n} ratio={ratio} p={p}")
+    S, f = P.Solver(g).stage_init(p, 77 + n)
+    torch_cuda.cuda.synchronize()
+    I = oracle_mod.Instance(g)
+    So, fo = I.init(77 + n, p)
+    np.testing.assert_array_equal(_np(S)[:, :I.nv], So)
+    np.testing.assert_array_equal(_np(f), fo)
+    assert not _np(S)[:, I.nv:].any()
