@@ -54,7 +54,7 @@ struct Layout {
     size_t vrc, vrec, cand, vinfo, nbr, rcl, rclo;
     size_t args, ctl, stats, Sstar;
     size_t S_all, S_off, S_tmp, f_all, f_tmp, uid, uid_tmp, hist, hist_tmp, hc, hc_tmp, cnt;
-    size_t tabu, planes, D, deg, adj, keys, rej, acc, pos, hkeys, hvals, partner, dpart;
+    size_t tabu, planes, D, deg, adj, keys, acc, pos, hkeys, hvals, partner, dpart;
     size_t queue;  // work queue of a persistent batched search launch led by this instance
     size_t total;
     int pow2_sel, hsize;
@@ -322,7 +322,6 @@ Layout plan(const plse_instance *h, int p) {
     L.adj = take(2 * m * kAdj);
     L.pow2_sel = next_pow2(std::max<int>(4, (int)m));
     L.keys = take(8 * (size_t)L.pow2_sel);
-    L.rej = take(4 * m);
     L.acc = take(4 * (size_t)p);
     L.pos = take(4 * m);
     L.hsize = next_pow2(std::max<int>(4, (int)m));
@@ -434,7 +433,6 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
     a.deg = at<int32_t>(h, L.deg);
     a.adj = at<uint16_t>(h, L.adj);
     a.keys_g = at<uint64_t>(h, L.keys);
-    a.rej = at<int32_t>(h, L.rej);
     a.acc = acc;
     a.pos = at<int32_t>(h, L.pos);
     a.p = p;

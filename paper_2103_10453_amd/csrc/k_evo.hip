@@ -327,12 +327,6 @@ __global__ __launch_bounds__(256) void close_kernel(const ArgList L) {
 }
 
 
-// One workgroup: keys (f, SELECT draw, index) sorted by a bitonic network,
-// then wave 0 scans them in order.  A candidate is accepted iff the population
-// is not full and no accepted candidate is close to it; the blocked set (the
-// union of the close lists of accepted candidates) lives in an LDS bitmap.
-// Lanes take 64 candidates at a time: the candidates up to the first
-// unblocked one with a non-empty close list are decided together.
 // Selection keys of P^all: f << 48 | SELECT draw << 16 | index (the order of
 // Alg. 4: e, then a random key, then the index), ~0 beyond m.
 __device__ __forceinline__ void select_keys(const SelectArgs &a, uint32_t gen, int q,
@@ -415,195 +409,213 @@ __global__ __launch_bounds__(256) void sort_global_kernel(const ArgList L, int k
     }
 }
 
+// One workgroup: keys (f, SELECT draw, index) sorted (here by a bitonic network
+// when they fit LDS), then scanned in that order.  A candidate is accepted iff
+// no accepted candidate before it is close to it and the population is not
+// full.  The scan takes a window of candidates, one per thread, and decides it
+// in rounds: the undecided mark the later ones of the window in their close
+// lists; who stays unmarked is accepted and blocks its list; who is blocked
+// drops out.  The result is that of deciding one by one: a candidate is only
+// accepted once all before it that could block it are decided.  A window ends
+// before an unblocked candidate whose close list exceeds kAdj; that one is
+// decided alone, its row of D read by all threads.
+//
+// Bound by the latency of a window's rounds, 5 us each.  32768 candidates in
+// families of about eight: 178 us with the keys sorted before; one wave that
+// decided 64 candidates at a time, one after the other in a scalar loop, took
+// 2.92 ms.  128 candidates: 11.5 us with their sort, from 17.5.
+__device__ __forceinline__ bool is_close(const SelectArgs &a, int16_t d) {
+    return a.spacing * (int64_t)d <= (int64_t)a.nv;
+}
+
 __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
     extern __shared__ __align__(16) uint8_t lds[];
+    __shared__ int s_stop[2], s_any[2], s_na;
+    __shared__ uint32_t s_wait[2][32], s_part[16];
     const SelectArgs a = arg_of<SelectArgs>(L);
-    int gen = a.gen_fixed;
-    if (gen == 0) {
-        if (a.ctl->stop) return;
-        gen = a.ctl->gen;
-    }
-    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x;
+    uint32_t gen;
+    if (!select_gen(a, &gen)) return;
+    const int tid = (int)threadIdx.x, nthr = (int)blockDim.x, lane = lane_id();
     const int m = a.m, P2 = a.pow2;
-    uint32_t *blocked = reinterpret_cast<uint32_t *>(lds);          // [(m+31)/32]
     const int nbw = (m + 31) / 32;
-    // keys in LDS: generated and sorted here; else already sorted in global
-    // memory by select_keys_kernel / sort_*_kernel
-    const int off_keys = (nbw * 4 + 15) & ~15;
-    uint64_t *K = a.keys_in_lds ? reinterpret_cast<uint64_t *>(lds + off_keys) : a.keys_g;
-    // close lists of the 64 candidates being scanned, staged per block, and
-    // each candidate's lane in the block being scanned (0xFF: not in it)
-    uint16_t *adjs = reinterpret_cast<uint16_t *>(lds + off_keys + (a.keys_in_lds ? P2 * 8 : 0));
-    uint8_t *inb = reinterpret_cast<uint8_t *>(adjs + 64 * kAdj);
-    if (a.keys_in_lds)
-        for (int q = tid; q < (P2 >> 2); q += nthr) select_keys(a, (uint32_t)gen, q, K);
-    for (int q = tid; q < nbw; q += nthr) blocked[q] = 0u;
+    const bool klds = a.keys_in_lds != 0;
+    // keys (then the candidates in order, and each candidate's place in it);
+    // with the keys in global memory the places alone
+    uint64_t *K = reinterpret_cast<uint64_t *>(lds);
+    uint16_t *rank = reinterpret_cast<uint16_t *>(lds);
+    uint16_t *order = rank + P2;
+    uint32_t *blocked = reinterpret_cast<uint32_t *>(
+        lds + (((klds ? (size_t)P2 * 8 : (size_t)m * 2) + 15) & ~(size_t)15));
+    uint32_t *accb = blocked + nbw;  // accepted, by place
+    uint32_t *gpre = accb + nbw;     // accepted before each group of 64 places
+
+    if (klds)
+        for (int q = tid; q < (P2 >> 2); q += nthr) select_keys(a, gen, q, K);
+    for (int q = tid; q < 2 * nbw; q += nthr) blocked[q] = 0u;
     for (int q = tid; q < m; q += nthr) *gptr(a.pos + q) = -1;
-    for (int q = tid; q < m; q += nthr) inb[q] = 0xFF;
+    if (tid < 32) s_wait[0][tid] = s_wait[1][tid] = 0u;
+    if (tid < 2) s_stop[tid] = m, s_any[tid] = 0;
+    if (tid == 0) s_na = 0;
     __syncthreads();
-    for (int k = 2; k <= (a.keys_in_lds ? P2 : 1); k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = tid; i < P2; i += nthr) {
-                const int ixj = i ^ j;
-                if (ixj > i) {
-                    const uint64_t x = K[i], y = K[ixj];
-                    const bool up = (i & k) == 0;
-                    if ((x > y) == up) {
-                        K[i] = y;
-                        K[ixj] = x;
+    if (klds) {
+        for (int k = 2; k <= P2; k <<= 1) {
+            for (int j = k >> 1; j > 0; j >>= 1) {
+                for (int i = tid; i < (P2 >> 1); i += nthr) {
+                    const int lo = bitonic_lo(i, j), hi = lo + j;
+                    const uint64_t x = K[lo], y = K[hi];
+                    if ((x > y) == ((lo & k) == 0)) {
+                        K[lo] = y;
+                        K[hi] = x;
+                    }
+                }
+                __syncthreads();
+            }
+        }
+        constexpr int kPer = 16;  // keys per thread: at most 2^14 keys fit LDS
+        uint32_t own[kPer];
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int r = tid + q * nthr;
+            own[q] = r < m ? (uint32_t)(K[r] & 0xFFFFull) : 0u;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kPer; ++q) {
+            const int r = tid + q * nthr;
+            if (r < m) {
+                order[r] = (uint16_t)own[q];
+                rank[own[q]] = (uint16_t)r;
+            }
+        }
+    } else {
+        for (int r = tid; r < m; r += nthr)
+            rank[(uint32_t)*gptr(a.keys_g + r) & 0xFFFFu] = (uint16_t)r;
+    }
+    __syncthreads();
+    auto order_at = [&](int r) -> int {
+        return klds ? (int)order[r] : (int)((uint32_t)*gptr(a.keys_g + r) & 0xFFFFu);
+    };
+    auto is_blocked = [&](int x) -> bool { return (blocked[x >> 5] >> (x & 31)) & 1u; };
+
+    int w0 = 0, par = 0, b = 0;
+    while (w0 < m) {
+        const int r = w0 + tid;
+        const bool valid = r < m;
+        const int x = valid ? order_at(r) : 0;
+        const int d = valid ? *gptr(a.deg + x) : 0;
+        u32x4 first = {0u, 0u, 0u, 0u};  // the close list's first eight
+        const uint8_t *list = reinterpret_cast<const uint8_t *>(a.adj + (size_t)x * kAdj);
+        if (d > 0) first = gload4(list);
+        bool und = valid && !is_blocked(x);
+        const uint64_t lng = ballot(und && d > kAdj);
+        if (lane == 0 && lng)
+            atomicMin(&s_stop[par], r + (int)__ffsll((unsigned long long)lng) - 1);
+        __syncthreads();
+        if (s_na >= a.p) break;
+        const int end = min(min(w0 + nthr, m), s_stop[par]);
+        par ^= 1;
+        if (tid == 0) s_stop[par] = m;
+        if (end == w0) {
+            const int x0 = order_at(w0);
+            const int16_t *row = a.D + (size_t)x0 * a.ld;
+            auto mark = [&](int y, int16_t dist) {
+                if (y != x0 && is_close(a, dist)) atomicOr(&blocked[y >> 5], 1u << (y & 31));
+            };
+            if ((a.ld & 7) == 0 && (m & 7) == 0) {
+                for (int y = 8 * tid; y < m; y += 8 * nthr) {
+                    const u32x4 q = gload4(row + y);
+                    const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+                    for (int t = 0; t < 8; ++t)
+                        mark(y + t, (int16_t)((w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu));
+                }
+            } else {
+                for (int y = tid; y < m; y += nthr) mark(y, *gptr(row + y));
+            }
+            __syncthreads();  // all have read s_na
+            if (tid == 0) {
+                accb[w0 >> 5] |= 1u << (w0 & 31);
+                ++s_na;
+            }
+            ++w0;
+            continue;
+        }
+        und = und && r < end;
+        // fn(place) for the members of the close list after this candidate
+        auto later = [&](auto fn) {
+            for (int q0 = 0; q0 < d; q0 += 8) {
+                const u32x4 e = q0 ? gload4(list + 2 * q0) : first;
+                const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const int y = (int)((ew[t >> 1] >> (16 * (t & 1))) & 0xFFFFu);
+                    if (q0 + t < d) {
+                        const int ry = rank[y];
+                        if (ry > r) fn(y, ry);
                     }
                 }
             }
+        };
+        bool accepted = false, marks = true;
+        for (;;) {
+            if (und && marks) {
+                marks = false;
+                later([&](int, int ry) {
+                    if (ry < end) {
+                        marks = true;
+                        atomicOr(&s_wait[b][(ry - w0) >> 5], 1u << ((ry - w0) & 31));
+                    }
+                });
+            }
+            if (ballot(und) && lane == 0) s_any[b] = 1;
             __syncthreads();
+            if (!s_any[b]) break;
+            const bool ready = und && !((s_wait[b][tid >> 5] >> (tid & 31)) & 1u);
+            if (ready) later([&](int y, int) { atomicOr(&blocked[y >> 5], 1u << (y & 31)); });
+            accepted = accepted || ready;
+            b ^= 1;
+            if (tid < 32) s_wait[b][tid] = 0u;
+            if (tid == 0) s_any[b] = 0;
+            __syncthreads();
+            und = und && !ready && !is_blocked(x);
         }
+        const uint64_t accm = ballot(accepted);
+        if (accepted) atomicOr(&accb[r >> 5], 1u << (r & 31));
+        if (lane == 0 && accm) atomicAdd(&s_na, (int)__popcll(accm));
+        w0 = end;
     }
-    if (tid >= 64) return;
-    const int lane = tid;
-    int na = 0, nr = 0;
-    bool full = false;
-    // Loads run one block ahead of the decisions: while a block is decided,
-    // the next block's candidates, degrees and close lists (all kAdj entries,
-    // whatever the degree) and the keys of the block after it are in flight.
-    auto key_at = [&](int r) -> uint64_t {
-        return r < m ? (a.keys_in_lds ? K[r] : *gptr(a.keys_g + r)) : 0ull;
-    };
-    constexpr int kAdjV = kAdj / 8;  // 16-byte vectors per close list
-    u32x4 an[kAdjV];
-    int xn = (int)(key_at(lane) & 0xFFFFull);
-    int dn = lane < m ? *gptr(a.deg + xn) : 0;
-#pragma unroll
-    for (int q = 0; q < kAdjV; ++q)
-        an[q] = gload4(reinterpret_cast<const u32x4 *>(a.adj + (size_t)xn * kAdj) + q);
-    uint64_t krn = key_at(64 + lane);
-    for (int base = 0; base < m && !full; base += 64) {
-        const int r = base + lane;
-        const bool valid = r < m;
-        const int x = xn, d = dn;
-        if (d > 0 && d <= kAdj) {
-            u32x4 *dst = reinterpret_cast<u32x4 *>(adjs + lane * kAdj);
-#pragma unroll
-            for (int q = 0; q < kAdjV; ++q) dst[q] = an[q];
-        }
-        xn = (int)(krn & 0xFFFFull);
-        dn = base + 64 + lane < m ? *gptr(a.deg + xn) : 0;
-#pragma unroll
-        for (int q = 0; q < kAdjV; ++q)
-            an[q] = gload4(reinterpret_cast<const u32x4 *>(a.adj + (size_t)xn * kAdj) + q);
-        krn = key_at(base + 128 + lane);
-        PLSE_WAVE_SYNC();
-        if (ballot(valid && d > kAdj) == 0) {
-            // every close list is complete: decide the block in scan order on
-            // 64-bit masks.  mk: the later candidates of this block that this
-            // one's close list holds; bl: the candidates blocked so far.
-            if (valid) inb[x] = (uint8_t)lane;
-            PLSE_WAVE_SYNC();
-            uint64_t mk = 0;
-            for (int q0 = 0; q0 < d; q0 += 8) {
-                // eight entries per 16-byte read, their lanes read together
-                const u32x4 e = reinterpret_cast<const u32x4 *>(adjs + lane * kAdj)[q0 >> 3];
-                const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
-                uint32_t js[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    // entries past d are not part of the list: clamp their index
-                    const uint32_t y = (ew[t >> 1] >> (16 * (t & 1))) & 0xFFFFu;
-                    js[t] = inb[min(y, (uint32_t)(m - 1))];
-                }
-#pragma unroll
-                for (int t = 0; t < 8; ++t)
-                    if (q0 + t < d && js[t] != 0xFFu && (int)js[t] > lane) mk |= 1ull << js[t];
-            }
-            PLSE_WAVE_SYNC();
-            if (valid) inb[x] = 0xFF;
-            uint64_t bl = ballot(valid && ((blocked[x >> 5] >> (x & 31)) & 1u));
-            const int nvalid = (int)__popcll(ballot(valid));
-            uint64_t accm = 0, rejm = 0;
-            int room = a.p - na;
-            for (int i = 0; i < nvalid; ++i) {
-                if ((bl >> i) & 1ull) {
-                    rejm |= 1ull << i;
-                    continue;
-                }
-                accm |= 1ull << i;
-                const uint32_t lo = readlane_u32((uint32_t)mk, i);
-                const uint32_t hi = readlane_u32((uint32_t)(mk >> 32), i);
-                bl |= ((uint64_t)hi << 32) | lo;
-                if (--room == 0) {
-                    full = true;
-                    break;
-                }
-            }
-            const bool am = (accm >> lane) & 1ull, rm = (rejm >> lane) & 1ull;
-            if (am) *gptr(a.acc + na + (int)rank_below(accm)) = x;
-            if (rm) *gptr(a.rej + nr + (int)rank_below(rejm)) = x;
-            na += (int)__popcll(accm);
-            nr += (int)__popcll(rejm);
-            // accepted candidates block their close lists for later blocks
-            if (am)
-                for (int q = 0; q < d; ++q) {
-                    const int y = adjs[lane * kAdj + q];
-                    atomicOr(&blocked[y >> 5], 1u << (y & 31));
-                }
-            PLSE_WAVE_SYNC();
-            continue;
-        }
-        // a close list longer than kAdj in the block: step from one
-        // unblocked candidate with a non-empty close list to the next
-        int pos = 0;
-        while (pos < 64) {
-            const bool blk = valid && ((blocked[x >> 5] >> (x & 31)) & 1u);
-            const bool act = valid && lane >= pos;
-            const uint64_t dep = ballot(act && !blk && d > 0);
-            const int L = dep ? (__ffsll((unsigned long long)dep) - 1) : 64;
-            const bool inr = act && lane < L;
-            const uint64_t accm = ballot(inr && !blk), rejm = ballot(inr && blk);
-            const int room = a.p - na;
-            const uint32_t ra = rank_below(accm);
-            if (inr && !blk && (int)ra < room) *gptr(a.acc + na + (int)ra) = x;
-            const uint32_t rr = rank_below(rejm);
-            if (inr && blk) *gptr(a.rej + nr + (int)rr) = x;
-            const int nacc = (int)__popcll(accm);
-            na += nacc < room ? nacc : room;
-            nr += (int)__popcll(rejm);
-            if (na >= a.p) {
-                full = true;
-                break;
-            }
-            if (L == 64) break;
-            const int xL = (int)shfl_u32((uint32_t)x, L), dL = (int)shfl_u32((uint32_t)d, L);
-            if (lane == 0) *gptr(a.acc + na) = xL;
-            ++na;
-            if (na >= a.p) {
-                full = true;
-                break;
-            }
-            if (dL <= kAdj) {
-                if (lane < dL) {
-                    const int y = adjs[L * kAdj + lane];
-                    atomicOr(&blocked[y >> 5], 1u << (y & 31));
-                }
-            } else {
-                const int16_t *row = a.D + (size_t)xL * a.ld;
-                for (int y = lane; y < m; y += 64)
-                    if (y != xL && a.spacing * (int64_t)*gptr(row + y) <= (int64_t)a.nv)
-                        atomicOr(&blocked[y >> 5], 1u << (y & 31));
-            }
-            PLSE_WAVE_SYNC();
-            pos = L + 1;
-        }
+    __syncthreads();
+    // accepted candidates in order; the rejected in order complete a short
+    // population (all candidates have been scanned then)
+    const int ng = (m + 63) / 64;
+    auto word = [&](int w) -> uint32_t { return w < nbw ? accb[w] : 0u; };
+    uint32_t c = tid < ng ? (uint32_t)(__popc(word(2 * tid)) + __popc(word(2 * tid + 1))) : 0u;
+    uint32_t total;
+    c = wave_excl_scan_dpp(c, &total);
+    if (lane == 0) s_part[tid >> 6] = total;
+    __syncthreads();
+    for (int w = 0; w < (tid >> 6); ++w) c += s_part[w];
+    if (tid < ng) gpre[tid] = c;
+    __syncthreads();
+    const int na = s_na;
+    for (int g = tid >> 6; g < ng; g += nthr >> 6) {
+        const int r = 64 * g + lane;
+        if (r >= m) continue;
+        const uint64_t bits = ((uint64_t)word(2 * g + 1) << 32) | word(2 * g);
+        const int before = (int)gpre[g] + (int)rank_below(bits);
+        const bool am = (bits >> lane) & 1ull;
+        const int at = am ? before : na + r - before;
+        if (at < a.p) *gptr(a.acc + at) = order_at(r);
     }
-    // fill rule: rejected candidates in scan order complete a short population
-    PLSE_WAVE_SYNC();
-    for (int t = lane; t < a.p - na; t += 64) *gptr(a.acc + na + t) = *gptr(a.rej + t);
 }
+
+// Threads: a window each, and half the keys of the sort.
+static int select_threads(int pow2) { return std::min(1024, std::max(64, pow2 / 2)); }
 
 size_t select_lds_bytes(int m, int pow2, bool keys_in_lds) {
-    const size_t b = ((size_t)((m + 31) / 32) * 4 + 15) & ~(size_t)15;
-    return b + (keys_in_lds ? (size_t)pow2 * 8 : 0) + (size_t)64 * kAdj * 2 +
-           (((size_t)m + 15) & ~(size_t)15);
+    const size_t keys = ((keys_in_lds ? (size_t)pow2 * 8 : (size_t)m * 2) + 15) & ~(size_t)15;
+    return keys + ((size_t)2 * ((m + 31) / 32) + (size_t)(m + 63) / 64) * 4;
 }
-
-
 
 // New population P_{t+1} = accepted candidates in acceptance order: rows,
 // f, uid ((gen << 32) | slot for members of P'), partner history (empty for
@@ -915,7 +927,7 @@ hipError_t launch_select(const ArgList &L, int count, size_t lds, int pow2, bool
                                k);
         }
     }
-    hipLaunchKernelGGL(select_kernel, dim3(1, count), dim3(1024), lds, stream, L);
+    hipLaunchKernelGGL(select_kernel, dim3(1, count), dim3(select_threads(pow2)), lds, stream, L);
     return hipGetLastError();
 }
 

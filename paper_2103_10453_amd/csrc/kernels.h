@@ -120,7 +120,6 @@ struct SelectArgs {
     const int32_t *deg;
     const uint16_t *adj;
     uint64_t *keys_g;        // [pow2] global scratch (when not in LDS)
-    int32_t *rej;            // [m] scratch
     int32_t *acc;            // [p] out
     int32_t *pos;            // [m] out: -1 (the fill; gather sets accepted ones)
     int32_t p, m, ld, nv, pow2, keys_in_lds, gen_fixed;

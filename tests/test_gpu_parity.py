@@ -838,3 +838,38 @@ def test_init_orders(torch_cuda, oracle_mod, n, ratio, p):
     np.testing.assert_array_equal(_np(S)[:, :I.nv], So)
     np.testing.assert_array_equal(_np(f), fo)
     assert not _np(S)[:, I.nv:].any()
+
+
+# --- population update: windows of candidates, long close lists, odd counts ------------------
+@pytest.mark.parametrize("global_sort", [0, 1])
+@pytest.mark.parametrize("p,group,symmetric", [
+    (31, 1, True),       # 62 candidates: less than a window, no close pairs
+    (65, 3, True),       # 130: a full window and a remainder
+    (515, 6, False),     # 1030: close in one direction only
+    (1025, 40, True),    # close lists beyond their capacity everywhere
+    (2500, 20, True),    # windows of 1024, chains of close candidates
+    (4096, 4096, True),  # two groups: nearly all rejected, then refilled
+])
+def test_select_windows(torch_cuda, oracle_mod, p, group, symmetric, global_sort):
+    """Alg. 4 equals the oracle where candidates come in groups of close ones:
+    `group` consecutive ids differ little (chains: neighbours are close, the
+    ends need not be), also with a D that is close one way only: an accepted
+    candidate's row names those it excludes, where the oracle reads a
+    candidate's own row (alike for distances), hence its transpose."""
+    _say(f"select windows p={p} group={group} symmetric={symmetric} sort={global_sort}")
+    g = gen.random_greedy(20, 0.5, 7)
+    s = P.Solver(g, select_global_sort=global_sort)
+    I = oracle_mod.Instance(g)
+    rng = np.random.default_rng(p)
+    m = 2 * p
+    ids = np.arange(m, dtype=np.int32)
+    D = np.where(ids[:, None] // group == ids[None, :] // group,
+                 np.abs(ids[:, None] - ids[None, :]) * (I.nv // 40 + 1), I.nv).astype(np.int32)
+    if not symmetric:
+        D[np.triu_indices(m, 1)] = I.nv
+    f = rng.integers(0, 5, size=m).astype(np.int32)
+    import torch
+    acc = s.stage_select(torch.from_numpy(f).cuda(), torch.from_numpy(D.astype(np.int16)).cuda(),
+                         3, 99 + p)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(_np(acc), oracle_mod.select(I.nv, p, 10, 99 + p, 3, f, D.T))
