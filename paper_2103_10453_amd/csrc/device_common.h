@@ -110,6 +110,12 @@ __device__ __forceinline__ u32x4 gload4(const void *p) {
 __device__ __forceinline__ u32x2 gload2(const void *p) {
     return *gptr(reinterpret_cast<const u32x2 *>(p));
 }
+// 16 bytes from an address of any alignment: rows of 16-bit distances of odd
+// length (global loads need none on gfx950, and the compiler knows).
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+__device__ __forceinline__ u32x4 gload4_any(const void *p) {
+    return *gptr(reinterpret_cast<const u32x4_any *>(p));
+}
 __device__ __forceinline__ void gstore4(void *p, u32x4 v) { *gptr(reinterpret_cast<u32x4 *>(p)) = v; }
 
 // ---------------------------------------------------------------------------

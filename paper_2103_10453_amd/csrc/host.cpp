@@ -707,7 +707,7 @@ int enqueue_rest(Session &S, hipStream_t s, hipEvent_t *mark = nullptr) {
     RC_TRY(launch_over(S.hs, &ArgBlock::hash,
                        [&](const ArgList &L, int c) { return launch_hash(L, c, p, hsize, s); }));
     RC_TRY(launch_over(S.hs, &ArgBlock::match,
-                       [&](const ArgList &L, int c) { return launch_match(L, c, p, s); }));
+                       [&](const ArgList &L, int c) { return launch_match(L, c, p, 2 * p, s); }));
     if (mark) HIP_TRY(hipEventRecord(mark[3], s));
     RC_TRY(launch_over(S.hs, &ArgBlock::aux,
                        [&](const ArgList &L, int c) { return launch_aux(L, c, p, s); }));
@@ -1917,7 +1917,7 @@ int plse_stage_match(plse_handle h, int32_t p, void *stream, const int16_t *D,
                               p, p, p, L.hsize, h->P.hist_len, 0, 0, 0u, 0u};
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_hash(single(h, &ArgBlock::hash), 1, p, L.hsize, s));
-    HIP_TRY(launch_match(single(h, &ArgBlock::match), 1, p, s));
+    HIP_TRY(launch_match(single(h, &ArgBlock::match), 1, p, p, s));
     return PLSE_OK;
 }
 

@@ -285,45 +285,57 @@ __global__ __launch_bounds__(256) void close_kernel(const ArgList L) {
     if (x >= a.m) return;
     const int lane = lane_id();
     const int16_t *row = a.D + (size_t)x * a.ld;
+    // spacing * d <= |V| for d up to this (spacing >= 1)
+    const int32_t dmax = readfirst((int32_t)min((int64_t)INT16_MAX, (int64_t)a.nv / a.spacing));
     uint32_t cnt = 0;
-    if ((a.ld & 7) == 0 && (a.m & 7) == 0) {
-        // eight distances per lane and load (16-byte rows of D), close list
-        // still in ascending order: lanes in order, then the lane's eight
-        for (int y0 = 0; y0 < a.m; y0 += 512) {
-            const int yb = y0 + lane * 8;
-            uint32_t fl = 0u;
-            if (yb < a.m) {
-                const u32x4 q = gload4(reinterpret_cast<const u32x4 *>(row + yb));
-                const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+    // Eight distances per lane and load, four loads in flight.  Few are close:
+    // the minimum of the eight decides for the wave whether any has to be
+    // looked at.  32768 rows: 376 us, 5.7 TB/s of D (413 us with each distance
+    // tested; rows of no multiple of eight were read two bytes at a time).
+    auto scan = [&](int y0, const u32x4 &q) {
+        typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        i16x2 m2 = __builtin_bit_cast(i16x2, w[0]);
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int16_t d = (int16_t)((w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu);
-                    const bool cl = (yb + t != x) && (a.spacing * (int64_t)d <= (int64_t)a.nv);
-                    fl |= (uint32_t)cl << t;
-                }
-            }
-            uint32_t total;
-            uint32_t pos = cnt + wave_excl_scan_dpp((uint32_t)__popc(fl), &total);
-            while (fl) {
-                const int t = __ffs(fl) - 1;
-                fl &= fl - 1u;
-                if (pos < (uint32_t)kAdj) *gptr(a.adj + (size_t)x * kAdj + pos) = (uint16_t)(yb + t);
-                ++pos;
-            }
-            cnt += total;
+        for (int t = 1; t < 4; ++t)
+            m2 = __builtin_elementwise_min(m2, __builtin_bit_cast(i16x2, w[t]));
+        const int yb = y0 + lane * 8;
+        const bool in = yb + 8 <= a.m;
+        if (ballot(in && min((int32_t)m2.x, (int32_t)m2.y) <= dmax) == 0ull) return;
+        uint32_t fl = 0u;
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const int32_t d = (int16_t)((w[t >> 1] >> (16 * (t & 1))) & 0xFFFFu);
+            fl |= (uint32_t)(in && yb + t != x && d <= dmax) << t;
         }
-        if (lane == 0) *gptr(a.deg + x) = (int32_t)cnt;
-        return;
+        // ascending order: lanes in order, then the lane's eight
+        uint32_t total;
+        uint32_t pos = cnt + wave_excl_scan_dpp((uint32_t)__popc(fl), &total);
+        while (fl) {
+            const int t = __ffs(fl) - 1;
+            fl &= fl - 1u;
+            if (pos < (uint32_t)kAdj) *gptr(a.adj + (size_t)x * kAdj + pos) = (uint16_t)(yb + t);
+            ++pos;
+        }
+        cnt += total;
+    };
+    constexpr int kAhead = 4;  // loads in flight per lane
+    const int full = a.m & ~7;
+    for (int y0 = 0; y0 < full; y0 += 512 * kAhead) {
+        u32x4 q[kAhead];
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h)
+            q[h] = gload4_any(row + min(y0 + 512 * h + lane * 8, full - 8));
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) scan(y0 + 512 * h, q[h]);
     }
-    for (int y0 = 0; y0 < a.m; y0 += 64) {
-        const int y = y0 + lane;
-        const bool cl = (y < a.m) && (y != x) && (a.spacing * (int64_t)row[y] <= (int64_t)a.nv);
-        const uint64_t msk = ballot(cl);
-        const uint32_t pos = cnt + rank_below(msk);
-        if (cl && pos < (uint32_t)kAdj) a.adj[(size_t)x * kAdj + pos] = (uint16_t)y;
-        cnt += (uint32_t)__popcll(msk);
-    }
-    if (lane == 0) a.deg[x] = (int32_t)cnt;
+    const int y = full + lane;
+    const bool cl = y < a.m && y != x && (int32_t)*gptr(row + min(y, a.m - 1)) <= dmax;
+    const uint64_t msk = ballot(cl);
+    const uint32_t pos = cnt + rank_below(msk);
+    if (cl && pos < (uint32_t)kAdj) *gptr(a.adj + (size_t)x * kAdj + pos) = (uint16_t)y;
+    cnt += (uint32_t)__popcll(msk);
+    if (lane == 0) *gptr(a.deg + x) = (int32_t)cnt;
 }
 
 
@@ -673,6 +685,9 @@ __device__ __forceinline__ uint32_t hash_uid(uint64_t u) {
 }
 
 
+// Words of an individual's bits of excluded entries of its row.
+__host__ __device__ inline int match_words(int cnt) { return (cnt + 31) / 32; }
+
 __global__ void hash_clear_kernel(const ArgList L) {
     const HashArgs a = arg_of<HashArgs>(L);
     if (a.ctl && a.ctl->stop) return;
@@ -699,37 +714,58 @@ __global__ void hash_insert_kernel(const ArgList L) {
 }
 
 
+// One wave per individual.  Its row of D is read eight distances a lane and
+// load, each made the key d << 16 | j (j < 2^15) whose minimum names the
+// partner.  Excluded entries (the history, and the individual itself) are bits
+// in the row's order, one byte per load, so that the loop has four operations
+// an entry and no further lookup.  Bound by the reads of D: 16384 rows of 16384
+// take 125 us (4.3 TB/s); two-byte loads, 64-bit keys and a lookup per entry
+// took 410 us.
+template <bool IDX>
+__device__ __forceinline__ uint32_t nearest(const MatchArgs &a, const int16_t *row,
+                                            const uint32_t *excl) {
+    const int lane = lane_id();
+    const int cnt = IDX ? a.m : a.p;
+    const uint8_t *ex8 = reinterpret_cast<const uint8_t *>(excl);
+    uint32_t lb = 0xFFFFFFFFu;
+#pragma unroll 4
+    for (int x0 = lane * 8; x0 + 8 <= cnt; x0 += 512) {
+        const u32x4 q = gload4_any(row + x0);
+        const uint32_t ex = ex8[x0 >> 3];
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+        u32x4 pa = {0u, 0u, 0u, 0u}, pb = pa;
+        if constexpr (IDX) pa = gload4(a.pos + x0), pb = gload4(a.pos + x0 + 4);
+        const uint32_t js[8] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            // pos is -1 for candidates not selected: a key of ~0
+            const uint32_t j = IDX ? js[t] : (uint32_t)(x0 + t);
+            const uint32_t d = (t & 1) ? w[t >> 1] & 0xFFFF0000u : w[t >> 1] << 16;
+            const uint32_t out = (uint32_t)((int32_t)(ex << (31 - t)) >> 31);
+            lb = min(lb, d | j | out);
+        }
+    }
+    const int x = (cnt & ~7) + lane;
+    if (x < cnt && !((excl[x >> 5] >> (x & 31)) & 1u)) {
+        const uint32_t j = IDX ? (uint32_t)*gptr(a.pos + x) : (uint32_t)x;
+        lb = min(lb, ((uint32_t)(uint16_t)*gptr(row + x) << 16) | j);
+    }
+    return wave_min_u32_dpp(lb);
+}
+
 __global__ __launch_bounds__(256) void match_kernel(const ArgList L) {
     extern __shared__ __align__(16) uint8_t lds[];
     const MatchArgs a = arg_of<MatchArgs>(L);
     if (a.ctl && a.ctl->stop) return;
     const int wv = (int)(threadIdx.x >> 6), lane = lane_id();
     const int i = (int)blockIdx.x * 4 + wv;
-    const int nbw = (a.p + 31) / 32;
+    const int nbw = match_words(a.idx ? a.m : a.p);
     uint32_t *excl = reinterpret_cast<uint32_t *>(lds) + (size_t)wv * nbw;
     if (i >= a.p) return;
-    for (int q = lane; q < nbw; q += 64) excl[q] = 0u;
-    PLSE_WAVE_SYNC();
     const int hcount = max(*gptr(a.hc + i), 0);
-    const int nh = min(hcount, a.hist_len);
-    for (int t = lane; t < nh; t += 64) {
-        const uint64_t u = *gptr(a.hist + (size_t)i * kHist + t);
-        uint32_t h = hash_uid(u) & (uint32_t)(a.hsize - 1);
-        for (;;) {
-            const uint64_t k = *gptr(a.hkeys + h);
-            if (k == u) {
-                const int s = *gptr(a.hvals + h);
-                atomicOr(&excl[s >> 5], 1u << (s & 31));
-                break;
-            }
-            if (k == ~0ull) break;
-            h = (h + 1) & (uint32_t)(a.hsize - 1);
-        }
-    }
-    PLSE_WAVE_SYNC();
     const int ai = a.idx ? *gptr(a.idx + i) : i;
     const int16_t *row = a.D + (size_t)ai * a.ld;
-    uint64_t best = ~0ull;
+    uint32_t best = 0xFFFFFFFFu;
     if (a.mode == 1) {
         // random matching (Section 5.3): uniform over the other p - 1
         int gen = a.gen_fixed;
@@ -738,63 +774,36 @@ __global__ __launch_bounds__(256) void match_kernel(const ArgList L) {
         int j = (int)(((uint64_t)w.x * (uint64_t)(uint32_t)(a.p - 1)) >> 32);
         j += (j >= i) ? 1 : 0;
         const int aj = a.idx ? *gptr(a.idx + j) : j;
-        best = ((uint64_t)(uint16_t)*gptr(row + aj) << 32) | (uint32_t)j;
-    }
-    for (int pass = 0; pass < 2 && best == ~0ull; ++pass) {
-        // branch-free body, unrolled: several index and distance loads in
-        // flight per lane
-        uint64_t lb = ~0ull;
-        if (a.idx && (a.ld & 7) == 0 && (a.m & 7) == 0) {
-            // the row in D order, eight entries per lane and 16-byte loads of
-            // D and of pos (which names the individual of each entry, -1 for
-            // candidates not selected)
-#pragma unroll 2
-            for (int x0 = lane * 8; x0 < a.m; x0 += 512) {
-                const u32x4 dq = gload4(row + x0);
-                const u32x4 pa = gload4(a.pos + x0);
-                const u32x4 pb = gload4(a.pos + x0 + 4);
-                const uint32_t dw[4] = {dq.x, dq.y, dq.z, dq.w};
-                const int32_t js[8] = {(int32_t)pa.x, (int32_t)pa.y, (int32_t)pa.z, (int32_t)pa.w,
-                                       (int32_t)pb.x, (int32_t)pb.y, (int32_t)pb.z, (int32_t)pb.w};
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const int j = js[t];
-                    const uint32_t d = (dw[t >> 1] >> (16 * (t & 1))) & 0xFFFFu;
-                    const int jc = j < 0 ? 0 : j;
-                    const bool ok = j >= 0 && j != i &&
-                                    (pass != 0 || !((excl[jc >> 5] >> (jc & 31)) & 1u));
-                    const uint64_t key = ok ? (((uint64_t)d << 32) | (uint32_t)j) : ~0ull;
-                    lb = key < lb ? key : lb;
+        best = ((uint32_t)(uint16_t)*gptr(row + aj) << 16) | (uint32_t)j;
+    } else {
+        for (int pass = 0; pass < 2 && best == 0xFFFFFFFFu; ++pass) {
+            for (int q = lane; q < nbw; q += 64) excl[q] = 0u;
+            PLSE_WAVE_SYNC();
+            const int nh = pass == 0 ? min(hcount, a.hist_len) : 0;
+            for (int t = lane; t < nh; t += 64) {
+                const uint64_t u = *gptr(a.hist + (size_t)i * kHist + t);
+                uint32_t h = hash_uid(u) & (uint32_t)(a.hsize - 1);
+                for (;;) {
+                    const uint64_t k = *gptr(a.hkeys + h);
+                    if (k == u) {
+                        const int s = *gptr(a.hvals + h);
+                        const int x = a.idx ? *gptr(a.idx + s) : s;
+                        atomicOr(&excl[x >> 5], 1u << (x & 31));
+                        break;
+                    }
+                    if (k == ~0ull) break;
+                    h = (h + 1) & (uint32_t)(a.hsize - 1);
                 }
             }
-        } else if (a.idx) {
-            // the row in D order (coalesced); pos names the individual of
-            // each entry, -1 for candidates not selected
-#pragma unroll 8
-            for (int x = lane; x < a.m; x += 64) {
-                const int j = *gptr(a.pos + x);
-                const uint32_t d = (uint16_t)*gptr(row + x);
-                const int jc = j < 0 ? 0 : j;
-                const bool ok = j >= 0 && j != i &&
-                                (pass != 0 || !((excl[jc >> 5] >> (jc & 31)) & 1u));
-                const uint64_t key = ok ? (((uint64_t)d << 32) | (uint32_t)j) : ~0ull;
-                lb = key < lb ? key : lb;
-            }
-        } else {
-#pragma unroll 8
-            for (int j = lane; j < a.p; j += 64) {
-                const uint32_t d = (uint16_t)*gptr(row + j);
-                const bool ok = j != i && (pass != 0 || !((excl[j >> 5] >> (j & 31)) & 1u));
-                const uint64_t key = ok ? (((uint64_t)d << 32) | (uint32_t)j) : ~0ull;
-                lb = key < lb ? key : lb;
-            }
+            if (lane == 0) atomicOr(&excl[ai >> 5], 1u << (ai & 31));
+            PLSE_WAVE_SYNC();
+            best = a.idx ? nearest<true>(a, row, excl) : nearest<false>(a, row, excl);
         }
-        best = wave_min_u64(lb);
     }
     if (lane == 0) {
-        const int j = (int)(uint32_t)best;
+        const int j = (int)(best & 0xFFFFu);
         a.partner[i] = j;
-        a.dpart[i] = (int32_t)(best >> 32);
+        a.dpart[i] = (int32_t)(best >> 16);
         if (a.hist_len > 0) {
             const int pos = hcount % a.hist_len;
             a.hist[(size_t)i * kHist + pos] = a.uid[j];
@@ -944,8 +953,8 @@ hipError_t launch_hash(const ArgList &L, int count, int p, int hsize, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_match(const ArgList &L, int count, int p, hipStream_t stream) {
-    const size_t lds = (size_t)4 * ((p + 31) / 32) * 4;
+hipError_t launch_match(const ArgList &L, int count, int p, int cnt, hipStream_t stream) {
+    const size_t lds = (size_t)4 * match_words(cnt) * 4;
     hipLaunchKernelGGL(match_kernel, dim3((p + 3) / 4, count), dim3(256), lds, stream, L);
     return hipGetLastError();
 }

@@ -211,7 +211,7 @@ hipError_t launch_select(const ArgList &L, int count, size_t lds, int pow2, bool
 size_t select_lds_bytes(int m, int pow2, bool keys_in_lds);
 hipError_t launch_gather(const ArgList &L, int count, int p, hipStream_t stream);
 hipError_t launch_hash(const ArgList &L, int count, int p, int hsize, hipStream_t stream);
-hipError_t launch_match(const ArgList &L, int count, int p, hipStream_t stream);
+hipError_t launch_match(const ArgList &L, int count, int p, int cnt, hipStream_t stream);  // cnt: row entries read
 hipError_t launch_aux(const ArgList &L, int count, int p, hipStream_t stream);
 hipError_t launch_ctl_reset(const ArgList &L, int count, hipStream_t stream);
 hipError_t launch_gen_begin(const ArgList &L, int count, hipStream_t stream);

@@ -873,3 +873,62 @@ def test_select_windows(torch_cuda, oracle_mod, p, group, symmetric, global_sort
                          3, 99 + p)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(_np(acc), oracle_mod.select(I.nv, p, 10, 99 + p, 3, f, D.T))
+
+
+# --- rows of distances of every length: 16-byte loads, remainders, unaligned rows -----------
+@pytest.mark.parametrize("p", [2, 3, 5, 7, 9, 17, 513, 1031])
+def test_match_row_lengths(torch_cuda, oracle_mod, p):
+    """Stage matching on rows that are no multiple of eight (and start at odd
+    16-byte offsets), with full histories (second pass) and all distances equal
+    (ties by slot), also from a matrix that starts two bytes off."""
+    import torch
+    _say(f"match rows p={p}")
+    s = P.Solver(gen.planted(10, 0.4, 0))
+    rng = np.random.default_rng(p)
+    for case in ("ties", "random", "all_seen", "offset"):
+        D = np.full((p, p), 7, np.int32) if case == "ties" else \
+            rng.integers(0, 30000, size=(p, p)).astype(np.int32)
+        uid = (rng.permutation(10 * p)[:p] + (7 << 32)).astype(np.uint64)
+        hist = np.zeros((p, 64), dtype=np.uint64)
+        hc = np.zeros(p, dtype=np.int32)
+        if case == "all_seen":
+            k = min(p, 64)
+            hist[:, :k] = uid[:k]
+            hc[:] = k
+        buf = torch.zeros(p * p + 1, dtype=torch.int16, device="cuda")
+        off = 1 if case == "offset" else 0
+        Dt = buf[off:off + p * p].view(p, p)
+        Dt.copy_(torch.from_numpy(D.astype(np.int16)))
+        hist_t = torch.from_numpy(hist.view(np.int64)).cuda()
+        hc_t = torch.from_numpy(hc).cuda()
+        partner, dpart = s.stage_match(Dt, torch.from_numpy(uid.view(np.int64)).cuda(), hist_t, hc_t)
+        torch.cuda.synchronize()
+        po, do, ho, hco = oracle_mod.match(D, uid, hist, hc)
+        np.testing.assert_array_equal(_np(partner), po, err_msg=case)
+        np.testing.assert_array_equal(_np(dpart), do, err_msg=case)
+        np.testing.assert_array_equal(_np(hist_t).view(np.uint64), ho, err_msg=case)
+        np.testing.assert_array_equal(_np(hc_t), hco, err_msg=case)
+
+
+@pytest.mark.parametrize("p,spacing", [(3, 10), (5, 1), (7, 1000000), (259, 10), (2051, 7)])
+def test_select_row_lengths(torch_cuda, oracle_mod, p, spacing):
+    """Alg. 4 on rows of 2p distances that are no multiple of eight, with close
+    ones at their ends and spacings from all candidates close to none."""
+    import torch
+    _say(f"select rows p={p} spacing={spacing}")
+    g = gen.random_greedy(20, 0.5, 7)
+    s = P.Solver(g, spacing=spacing)
+    nv = oracle_mod.Instance(g).nv
+    rng = np.random.default_rng(p)
+    m = 2 * p
+    D = rng.integers(nv // 20, 60 * nv // 61 + 1, size=(m, m))
+    far = rng.random((m, m)) < 0.995
+    D = np.where(far, np.minimum(D, D.T) + nv // spacing, nv // spacing)
+    D[:, -1] = D[:, 0]
+    D = np.minimum(D, D.T).astype(np.int32)
+    np.fill_diagonal(D, 0)
+    f = rng.integers(0, 3, size=m).astype(np.int32)
+    acc = s.stage_select(torch.from_numpy(f).cuda(), torch.from_numpy(D.astype(np.int16)).cuda(),
+                         2, p)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(_np(acc), oracle_mod.select(nv, p, spacing, p, 2, f, D))
