@@ -13,34 +13,63 @@
 // Candidate rows.  The moves of vertex v are the colours of {0} u D*(v)
 // (0: uncolour), kept ascending at cand[v][0 .. d] with d = |D*(v)|, TS
 // positions per vertex; the tabu expiry of each move sits at the same
-// position of tabu[v].  An iteration cuts the rows of its eligible vertices
-// into chunks of CH consecutive positions and deals the chunks to the 64
-// lanes round by round, so every lane evaluates CH moves per round whatever
-// the domain sizes are.
+// position of tabu[v].  The rows are cut into chunks of CH consecutive
+// positions; one lane evaluates one chunk.
+//
+// Two forms of an iteration.
+//   Listed: the chunks of the eligible vertices V_0 u C(S) stay with their
+//   lanes from one iteration to the next, one chunk per lane in up to
+//   kPlitsSlots slots: vertex, row, column, colour and candidate colours in
+//   registers, in no order (a move's id decides ties, not where it is found).
+//   A move frees the lanes of the vertices that leave and gives the first free
+//   lanes to those that join, about one each, so an iteration neither scans
+//   for eligible vertices nor deals chunks nor loads candidates.  Conflict
+//   counts and expiries are read afresh: keeping them with the chunks too
+//   makes every move update all slots, which costs more than the reads.
+//   Dealt: while the chunks do not fit (the first descent from an offspring,
+//   mostly), they are dealt to the lanes round by round from the eligibility
+//   bitmap, which both forms keep.
+//   Chunks of 8 in four slots hold 96 % of the iterations at n = 50, half
+//   prefilled (24 eligible vertices of 13 colours), and at n = 70, 70 %.
 //
 // Per wave (LDS): S[stride] colours, rowcnt|colcnt, the eligibility bitmap of
 //   V_0 u C(S), tm8[|V|] (per vertex: whether this phase wrote its tabu row,
 //   and its latest tabu expiry relative to a base advanced by 128 iterations
 //   at a time, 255 = "treat as live"; a vertex not live has no tabu move),
-//   the 64 eligible vertices being dealt, a ring of chunk descriptors, the
-//   colour halves of the iteration's tie values and bit planes of the
-//   vertices' chunk counts.
+//   the colour halves of the iteration's tie values; for the dealt form the
+//   eligible vertices being dealt, a ring of chunk descriptors and bit planes
+//   of the vertices' chunk counts.
 // Per individual (HBM): tabu[|V|][TS] "allowed from" iteration of every move,
 //   read only for vertices with a live entry; all zero between phases (each
 //   phase clears the rows it wrote).
 //
 // One iteration:
-//   1. eligible vertices V_0 u C(S) from the bitmap (wave prefix sum);
-//   2. chunks of their candidate rows, CH moves per lane and round: move value
-//      from the row/column counts, admissibility from tabu and aspiration,
-//      best key per lane: (value, tie value) above the move id v (n+1) + k,
-//      the tie value being the top half of fmix32(w1 ^ v) ^ fmix32(w2 ^ k)
-//      for the iteration's random words w1, w2;
-//   3. a DPP wave minimum of the upper key words, then (only when several
-//      lanes hold it) of their move ids, picks the unique best admissible
-//      move;
-//   4. counts, colour, eligibility bits of the row/column vertices holding the
-//      old or new colour, tenure, tabu entry, best-solution snapshot.
+//   1. the chunks (listed, or dealt from the bitmap): move value from the
+//      row/column counts, admissibility from tabu and aspiration, best key per
+//      lane: (value, tie value) above the move id (v, k), the tie value being
+//      the top half of fmix32(w1 ^ v) ^ fmix32(w2 ^ k) for the iteration's
+//      random words w1, w2;
+//   2. a DPP wave minimum of the keys, then (only when several lanes hold it)
+//      of their move ids, picks the unique best admissible move;
+//   3. counts, colour, eligibility of the row/column vertices holding the old
+//      or new colour (and the list), tenure, tabu entry, best-solution
+//      snapshot.
+//
+// Bound by instruction issue: a lone wave takes about 7 cycles an instruction
+// of any kind, and 16 waves per CU keep the VALU busy for two thirds of the
+// time.  Per iteration at n = 50, half prefilled, |P| = 4096: 410 VALU, 294
+// scalar, 57 LDS instructions and 40 branches; with every iteration dealt 502,
+// 273, 68 and 55.  ns per iteration over the device (4096 searches) and us per
+// iteration of a lone search, dealt -> listed:
+//   n = 50, 50 % prefilled: 1.31 -> 1.21 ns, 2.74 -> 2.33 us
+//   n = 70, 70 %:           4.06 -> 3.18 ns, 6.38 -> 4.75 us
+//   n = 70, 80 %, PartialCol (chunks of 4): 2.94 -> 1.74 ns
+//   n = 100, 50 %:          8.72 -> 7.59 us;   n = 10: 2.58 -> 2.0 us
+// What keeps the scalar side small: wave-uniform values are made uniform for
+// the compiler (readfirst, scalar loads of arguments and tables), and each loop
+// has one exit, so that the list's registers are not copied at its joins.
+#include <type_traits>
+
 #include "device_common.h"
 #include "kernels.h"
 
@@ -56,7 +85,7 @@ struct WaveState {
                        // m in 2..254: latest expiry = base + m - 1; 255: treat as live
     uint16_t *stage;   // [kPlitsStage] eligible vertices of consecutive ranks
     uint32_t *ring;    // chunk descriptors: vertex | chunk index << 16 | live << 31
-    uint16_t *hk;      // [n+1] colour halves of the iteration's tie values
+    uint32_t *hk;      // [n+1] colour halves of the iteration's tie values
     uint32_t *planes;  // [B][W] bit b of floor(|D*(v)| / CH) (chunks per row - 1)
     int nplanes;
 };
@@ -70,10 +99,17 @@ struct Cnt {
 };
 
 struct Scal {
-    int64_t F, Fbest;
     int32_t f, c, nC;  // uncoloured, conflicting edges, conflicting vertices
     int32_t fbest, cbest;
 };
+
+// The lane id for code that seldom runs: addresses formed from it are not kept
+// in registers around the search's loops.
+__device__ __forceinline__ int rare_lane() {
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 
 // Position of colour k in a candidate row with 128-bit domain mask a: 0 for
 // k = 0, else 1 + the number of domain colours below k.
@@ -88,7 +124,7 @@ __device__ __forceinline__ uint32_t position_in(const u32x4 a, int k) {
 // S from `src`; row/column colour counts; eligibility bitmap; f, c, |C(S)|.
 __device__ void setup_state(const DevInstance &I, const uint8_t *src, const WaveState &ws,
                             Scal &sc) {
-    const int lane = lane_id();
+    const int lane = rare_lane();
     const int n = I.n, nv = I.nv, np1 = n + 1;
     for (int q = lane; q < (I.stride >> 4); q += 64)
         reinterpret_cast<u32x4 *>(ws.S)[q] = gload4(reinterpret_cast<const u32x4 *>(src) + q);
@@ -135,19 +171,26 @@ __device__ void setup_state(const DevInstance &I, const uint8_t *src, const Wave
 }
 
 __device__ __forceinline__ void snapshot(const DevInstance &I, const uint8_t *S, uint8_t *dst) {
-    for (int q = lane_id(); q < (I.stride >> 4); q += 64)
+    for (int q = rare_lane(); q < (I.stride >> 4); q += 64)
         gstore4(reinterpret_cast<u32x4 *>(dst) + q, reinterpret_cast<const u32x4 *>(S)[q]);
 }
 
 // Zero the tabu rows this phase wrote (vertices with a nonzero mark).
 __device__ void clear_tabu(const DevInstance &I, uint32_t *tabu, const WaveState &ws) {
     const int q4 = I.ts >> 2;
-    for (int v = lane_id(); v < I.nv; v += 64) {
+    for (int v = rare_lane(); v < I.nv; v += 64) {
         if (ws.tm8[v] != 0) {
             u32x4 *tb = reinterpret_cast<u32x4 *>(tabu + (size_t)v * I.ts);
             for (int t = 0; t < q4; ++t) gstore4(tb + t, u32x4{0u, 0u, 0u, 0u});
         }
     }
+}
+
+// base + off: a 32-bit offset from a uniform base needs no 64-bit address
+// arithmetic per lane.
+template <typename T>
+__device__ __forceinline__ const T *at_byte(const void *base, uint32_t off) {
+    return reinterpret_cast<const T *>(static_cast<const uint8_t *>(base) + off);
 }
 
 // CH consecutive candidate colours (bytes) and their tabu expiries.
@@ -199,6 +242,54 @@ struct Chunk<8> {
     }
 };
 
+// Slots of the chunk list, and the mark of a free lane (no vertex has it).
+constexpr int kPlitsSlots = 4;
+constexpr uint32_t kFreeLane = 0xFFFFFFFFu;
+constexpr int32_t kZeroMove = 0x1000;       // e of a move that changes nothing
+constexpr int32_t kOwnUncoloured = 0x1FFF;  // above every move's
+constexpr uint32_t kNoMove = 0xFFFFFFFFu >> 3;
+
+// Byte t of a chunk's colours.
+__device__ __forceinline__ uint32_t colour_at(uint64_t cw, uint32_t t) {
+    return __builtin_amdgcn_perm((uint32_t)(cw >> 32), (uint32_t)cw, t | 0x0C0C0C00u);
+}
+__device__ __forceinline__ uint32_t colour_at(uint32_t cw, uint32_t t) {
+    return __builtin_amdgcn_perm(0u, cw, t | 0x0C0C0C00u);
+}
+
+// A lane's best move: value and tie value, its id (vertex << 7 | colour) and
+// its vertex's payload.
+struct Best {
+    uint32_t hi, id, pay;
+};
+
+// Instance tables at wave-uniform addresses: scalar loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *cptr(const T *p) {
+    return (const __attribute__((address_space(4))) T *)p;
+}
+
+// v * u of 24-bit factors, u uniform (a full 32-bit product takes four times
+// as long).
+__device__ __forceinline__ uint32_t mul24(uint32_t v, uint32_t u) {
+    uint32_t x;
+    asm("v_mul_u32_u24 %0, %1, %2" : "=v"(x) : "s"(u), "v"(v));
+    return x;
+}
+
+// A structure at a wave-uniform address, into scalar registers (read through
+// an ordinary pointer it would be held in vector registers).
+template <typename T>
+__device__ __forceinline__ T cload(const void *p) {
+    struct Words {
+        uint32_t w[sizeof(T) / 4];
+    } x;
+    static_assert(sizeof(T) % 4 == 0, "whole words");
+#pragma unroll
+    for (size_t i = 0; i < sizeof(T) / 4; ++i) x.w[i] = cptr(static_cast<const uint32_t *>(p))[i];
+    return __builtin_bit_cast(T, x);
+}
+
 // PH 1, 2: the two phases of Section 3.3.  PH 3: PartialCol (Section 3.7),
 // the search of Partial-MPMA over legal partial colourings: the eligible
 // vertices are the uncoloured ones (a legal colouring has no conflicts), a
@@ -208,21 +299,20 @@ template <int CH, int PH>
 __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                           uint32_t gen, const uint8_t *src, uint8_t *out, uint32_t *tabu,
                           const WaveState &ws, Scal &sc, Cnt &ucnt, uint32_t &lane_cands) {
-    const DevInstance I = a.I;  // by value: the pointers the search uses stay in registers
+    const DevInstance &I = a.I;
     const int lane = lane_id();
     const int n = I.n, nv = I.nv, np1 = n + 1, TS = I.ts;
-    // F = phi_den f + phi_num c: phase 1 phi = 1/2, phase 2 phi = |V|;
+    // F = f + phi c: phase 1 phi = 1/2 (compared as 2 f + c), phase 2 phi = |V|;
     // PartialCol: F = f (c stays 0)
-    const int32_t phi_num = (PH == 1 || PH == 3) ? 1 : nv;
-    const int32_t phi_den = (PH == 1) ? 2 : 1;
     const uint32_t tag = PH == 1 ? TAG_PLITS1 : (PH == 2 ? TAG_PLITS2 : TAG_PARTIAL);
-    // Move values on a 16-bit scale e ordered like delta: e = delta when the
-    // phase's values fit (phase 1, and phase 2 with |V| <= 64); otherwise
-    // e = 4 dc + df, which orders moves as |V| dc + df does since |df| <= 1
-    // and |V| >= 3.  Keys carry e + 2^15.
-    const bool squeeze = (PH == 2 && nv > 64);
-    const int32_t eA = (PH != 2) ? 1 : (squeeze ? 4 : nv);  // per unit of dc
-    const int32_t eB = (PH == 1) ? 2 : 1;                   // per unit of df
+    // Move values on a 13-bit scale e ordered like delta: e = delta, but in
+    // phase 2 e = 4 dc + df, which orders moves as |V| dc + df does since
+    // |df| <= 1 (with fewer than three vertices no two moves at a time differ).
+    // Keys carry e + 2^12 over the 16-bit tie value over the move's position in
+    // its chunk.
+    constexpr int kShift = PH == 2 ? 2 : 0;
+    constexpr int32_t eA = 1 << kShift;        // per unit of dc
+    constexpr int32_t eB = PH == 1 ? 2 : 1;    // per unit of df
     const uint32_t alpha_n = (uint32_t)a.P.alpha_num, alpha_d = (uint32_t)a.P.alpha_den;
     const uint32_t m_alpha = 0xFFFFFFFFu / alpha_d;
     uint8_t *rowH = ws.H;
@@ -230,8 +320,6 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
 
     setup_state(I, src, ws, sc);
     if (src != out) snapshot(I, ws.S, out);
-    sc.F = (int64_t)phi_den * sc.f + (int64_t)phi_num * sc.c;
-    sc.Fbest = sc.F;
     sc.fbest = sc.f;
     sc.cbest = sc.c;
     const int W = (nv + 31) >> 5;
@@ -249,19 +337,71 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
     const uint32_t ln_odd = (lane & 1) ? 0xFFFFFFFFu : 0u;  // column count
     PLSE_WAVE_SYNC();
 
-    for (int64_t it = 0; it < iters; ++it) {
-        const uint32_t itu = (uint32_t)it;
+    // The chunk list: one chunk per lane and slot (vertex | chunk << 16 and, in
+    // the vertex's first chunk, |D*(v)| << 24; the vertex's payload and the
+    // chunk's colours), in any order.
+    constexpr int R = kPlitsSlots;
+    using Colours = decltype(Chunk<CH>::colours(nullptr));
+    uint32_t sent[R], spay[R];
+    Colours scw[R];
+    uint32_t slots = 1u;  // slots in use
+    // Free the lanes of vertex u.
+    auto drop = [&](uint32_t u) {
+#pragma unroll
+        for (int q = 0; q < R; ++q)
+            sent[q] = (sent[q] & 0xFFFFu) == u ? kFreeLane : sent[q];
+    };
+    // Give the chunks of vertex u the first free lanes; false if too few.
+    auto enlist = [&](uint32_t u, uint32_t colour) -> bool {
+        const uint32_t vi = *cptr(I.vinfo + u);
+        const uint8_t *row = I.cand + (size_t)u * TS;
+        const uint32_t d = (vi >> 16) & 0xFFu, pay = (vi & 0xFF00FFFFu) | (colour << 16);
+        uint32_t need = d / CH + 1u, first = 0u;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            if (need == 0u) break;
+            const uint64_t room = ballot(sent[q] == kFreeLane);
+            const uint32_t at = rank_below(room);
+            const bool me = sent[q] == kFreeLane && at < need;
+            const uint32_t ci = first + at;
+            if (me) scw[q] = Chunk<CH>::colours(row + ci * CH);
+            sent[q] = me ? u | (ci << 16) | (ci == 0u ? d << 24 : 0u) : sent[q];
+            spay[q] = me ? pay : spay[q];
+            const uint32_t got = min(need, (uint32_t)__popcll(room));
+            first += got;
+            need -= got;
+            slots = max(slots, (uint32_t)q + 1u);
+        }
+        return need == 0u;
+    };
+
+    // Counters of the last 64 iterations.
+    uint32_t n_elig = 0u, n_nupd = 0u, n_ends = 0u;
+    auto tally = [&]() {
+        ucnt.elig += n_elig;
+        ucnt.nupd += n_nupd;
+        ucnt.cupd += 2u * n_ends;
+        n_elig = n_nupd = n_ends = 0u;
+    };
+    // iterations of a phase: below 2^31
+    const uint32_t end = (uint32_t)iters;
+    uint32_t itu = 0u, w0 = 0u, w1 = 0u, w2 = 0u;
+    // Random words, expiry marks, the last move's tabu entry and the colour
+    // halves of the tie values (nothing counts twice where an iteration is
+    // begun again in the dealt form).
+    auto begin = [&]() {
         if ((itu & 63u) == 0u) {
-            const U4 rw = draw(a.seed_lo, a.seed_hi, slot, gen, tag, itu + (uint32_t)lane);
+            const U4 rw = draw(a.seed_lo, a.seed_hi, slot, gen, tag, itu + (uint32_t)rare_lane());
+            tally();
             wx = rw.x;
             wy = rw.y;
             wz = rw.z;
         }
-        if ((itu & 127u) == 0u && itu != 0u) {
+        if ((itu & 127u) == 0u && tbase != itu) {
             // advance the base: marks drop by 128 (expired ones to 1), 255 stays
             tbase += 128u;
             PLSE_WAVE_SYNC();
-            for (int q = lane; q < (nv + 3) >> 2; q += 64) {
+            for (int q = rare_lane(); q < (nv + 3) >> 2; q += 64) {
                 const uint32_t x = reinterpret_cast<uint32_t *>(ws.tm8)[q];
                 uint32_t y = 0u;
 #pragma unroll
@@ -278,188 +418,117 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             const uint32_t mark = rel > 253u ? 255u : rel + 1u;
             if (mark > ws.tm8[pend_tv]) ws.tm8[pend_tv] = (uint8_t)mark;
         }
-        const uint32_t w0 = readlane_u32(wx, (int)(itu & 63u));
-        const uint32_t w1 = readlane_u32(wy, (int)(itu & 63u));
-        const uint32_t w2 = readlane_u32(wz, (int)(itu & 63u));
-        // colour halves of the tie values (written first: independent of the
-        // eligibility scan, which covers their latency)
-        if (lane <= n) ws.hk[lane] = (uint16_t)(fmix32(w2 ^ (uint32_t)lane) >> 16);
-        if (lane + 64 <= n) ws.hk[lane + 64] = (uint16_t)(fmix32(w2 ^ (uint32_t)(lane + 64)) >> 16);
-        // 1. eligible vertices (ascending rank over the bitmap): their number
-        //    m, and the first kPlitsStage of them staged for dealing
-        uint32_t m = 0;
-        for (int wb = 0; wb < W; wb += 64) {
-            const int w = wb + lane;
-            uint32_t bits = (w < W) ? ws.bm[w] : 0u;
-            uint32_t total;
-            uint32_t pos = m + wave_excl_scan_dpp((uint32_t)__popc(bits), &total);
-#pragma unroll 1
-            while (bits && pos < (uint32_t)kPlitsStage) {
-                const int b = __ffs(bits) - 1;
-                bits &= bits - 1u;
-                ws.stage[pos++] = (uint16_t)(w * 32 + b);
-            }
-            m += total;
-        }
-        if (m == 0) break;  // F = 0: complete legal colouring
-        PLSE_WAVE_SYNC();
-        ucnt.iters++;
-        ucnt.elig += m;
-
-        // 2. best admissible one-move per lane over the chunk rounds.
-        //    Aspiration F + delta < F* is e + 2^15 < teb.
-        int32_t te;
-        if (!squeeze) {
-            const int64_t gap = sc.Fbest - sc.F;  // <= 0
-            te = gap < -(1ll << 30) ? -(1 << 30) : (int32_t)gap;
-        } else {
-            te = squeezed_bound(sc.fbest - sc.f, sc.cbest - sc.c, nv);
-        }
-        const int32_t teb = te + 0x8000;
-        // per lane: upper key word of its best move (value, tie value), the
-        // move's vertex and colour, and the vertex's payload.  A lane meets
-        // its moves in ascending id order, so keeping the first of equal
-        // upper words keeps the smallest id among them.
-        uint32_t lhi = 0xFFFFFFFFu, lv = 0u, lk = 0u, lpay = 0u;
         if (pend_off != 0xFFFFFFFFu) gptr(tabu)[pend_off] = pend_val;
-        uint32_t head = 0u, tail = 0u, g = 0u;
-        uint32_t sbase = 0u;  // rank of stage[0]
-        for (;;) {
-            // once the ring is empty, deal the rows of the next 64 eligible
-            // vertices into it
-            if (head == tail && g < m) {
-                head = tail = 0u;
-                if (g >= sbase + (uint32_t)kPlitsStage) {
-                    // stage eligible vertices of rank g .. g+kPlitsStage-1
-                    // (the bitmap does not change within the iteration)
-                    PLSE_WAVE_SYNC();
-                    sbase = g;
-                    const uint32_t gend = g + (uint32_t)kPlitsStage;
-                    uint32_t base = 0;
-                    for (int wb = 0; wb < W && base < gend; wb += 64) {
-                        const int w = wb + lane;
-                        uint32_t bits = (w < W) ? ws.bm[w] : 0u;
-                        uint32_t total;
-                        uint32_t pos = base + wave_excl_scan_dpp((uint32_t)__popc(bits), &total);
-#pragma unroll 1
-                        while (bits && pos < gend) {
-                            const int b = __ffs(bits) - 1;
-                            bits &= bits - 1u;
-                            if (pos >= g) ws.stage[pos - g] = (uint16_t)(w * 32 + b);
-                            ++pos;
-                        }
-                        base += total;
-                    }
-                    PLSE_WAVE_SYNC();
-                }
-                const uint32_t e = g + (uint32_t)lane;
-                uint32_t v = 0u, nch = 0u, ent = 0u;
-                if (e < m) {
-                    v = ws.stage[e - sbase];
-                    // chunk count and liveness of v, read together: planes 0
-                    // and 1 (or 0 twice), further planes only when present
-                    const int vw = (int)(v >> 5);
-                    const bool p0ok = ws.nplanes > 0, p1ok = ws.nplanes > 1;
-                    const uint32_t q0 = p0ok ? ws.planes[vw] : 0u;
-                    const uint32_t q1 = p1ok ? ws.planes[W + vw] : 0u;
-                    const uint32_t tm = ws.tm8[v];
-                    uint32_t code = ((q0 >> (v & 31u)) & 1u) | (((q1 >> (v & 31u)) & 1u) << 1);
-                    if (ws.nplanes > 2) {
+        w0 = readlane_u32(wx, (int)(itu & 63u));
+        w1 = readlane_u32(wy, (int)(itu & 63u));
+        w2 = readlane_u32(wz, (int)(itu & 63u));
+        if (lane <= n) ws.hk[lane] = fmix32(w2 ^ (uint32_t)lane) >> 16 << 3;
+        if (n >= 64 && lane + 64 <= n)
+            ws.hk[lane + 64] = fmix32(w2 ^ (uint32_t)(lane + 64)) >> 16 << 3;
+        PLSE_WAVE_SYNC();
+    };
+    // Aspiration F + delta < F*: keys below this.
+    auto bound = [&]() -> uint32_t {
+        const int32_t te = PH == 2 ? squeezed_bound(sc.fbest - sc.f, sc.cbest - sc.c, nv)
+                         : (PH == 1 ? 2 * (sc.fbest - sc.f) + (sc.cbest - sc.c) : sc.fbest - sc.f);
+        return (uint32_t)max(te + kZeroMove, 0) << 19;
+    };
+    auto eligible = [&]() -> uint32_t { return (uint32_t)(PH == 3 ? sc.f : sc.f + sc.nC); };
+    // The best move of chunk ci of vertex v (pay: row | column << 8 |
+    // colour << 16 | degree << 24) against the lane's best so far.  Without
+    // `exact` the vertex's own colour is no exception: it then counts two
+    // conflicts more than the vertex has (kOwnUncoloured if uncoloured).
+    auto look = [&](auto exact, Best &b, uint32_t teb, uint32_t v, uint32_t ci, bool live, uint32_t pay, Colours cw) {
+        uint32_t tv[CH];
 #pragma unroll
-                        for (int b = 2; b < 6; ++b)
-                            if (b < ws.nplanes)
-                                code |= ((ws.planes[b * W + vw] >> (v & 31u)) & 1u) << b;
-                    }
-                    nch = code + 1u;  // ceil((d + 1) / CH)
-                    // a vertex not live has no tabu move this iteration
-                    const bool live = tm == 255u || tm > itu - tbase + 1u;
-                    ent = v | ((uint32_t)live << 31);
-                }
-                uint32_t total;
-                const uint32_t at = tail + wave_excl_scan_dpp(nch, &total);
-#pragma unroll 1
-                for (uint32_t t = 0; t < nch; ++t) ws.ring[at + t] = ent | (t << 16);
-                tail += total;
-                g += 64u;
-                PLSE_WAVE_SYNC();
+        for (int t = 0; t < CH; ++t) tv[t] = 0u;
+        if (live)
+            Chunk<CH>::tabu(at_byte<uint32_t>(tabu, (mul24(v, (uint32_t)TS) + ci * CH) * 4u), tv);
+        const uint32_t s = (pay >> 16) & 0xFFu;
+        const uint8_t *rH = rowH + __umul24(pay & 0xFFu, (uint32_t)np1);
+        const uint8_t *cH = colH + __umul24((pay >> 8) & 0xFFu, (uint32_t)np1);
+        // Up to four moves at a time.  Their LDS reads are issued together, the
+        // second four's between the keys and the comparisons of the first
+        // (the scheduler, saving registers, would wait for each pair).
+        constexpr int kG = CH < 4 ? CH : 4;
+        uint32_t kk[kG], ra[kG], ca[kG], hkv[kG], key[kG];
+        auto fetch = [&](int g) {
+#pragma unroll
+            for (int t = 0; t < kG; ++t) kk[t] = (uint32_t)(cw >> (8 * (g + t))) & 0xFFu;
+#pragma unroll
+            for (int t = 0; t < kG; ++t) ra[t] = rH[kk[t]], ca[t] = cH[kk[t]];
+#pragma unroll
+            for (int t = 0; t < kG; ++t) hkv[t] = ws.hk[kk[t]];
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const uint32_t sr = rH[s], sc_ = cH[s];
+        fetch(0);
+        // e = eB df + eA (conf(v,k) - conf(v,s)), df = -1 when v was
+        // uncoloured (the counts of colour 0 are 0), +1 for the uncolour
+        // move (k = 0, position 0)
+        const uint32_t hv = fmix32(w1 ^ v) >> 16 << 3;
+        const int32_t base = kZeroMove + (s ? 2 * eA : -eB) - eA * (int32_t)(sr + sc_);
+        const int32_t base0 = ci != 0u ? base
+                              : (!decltype(exact)::value && s == 0u ? kOwnUncoloured : base + eB);
+        // the parts of the keys that do not depend on the colour
+        const uint32_t kv = ((uint32_t)base << 19) + hv, kv0 = ((uint32_t)base0 << 19) + hv;
+        uint32_t best = 0xFFFFFFFFu;
+#pragma unroll
+        for (int g = 0; g < CH; g += kG) {
+            bool own[kG];
+#pragma unroll
+            for (int t = 0; t < kG; ++t) {
+                const uint32_t x = __builtin_amdgcn_bitop3_b32(
+                    g + t == 0 ? kv0 : kv, hkv[t], (uint32_t)(g + t), 0xBE);  // (a ^ b) | c
+                key[t] = ((ra[t] + ca[t]) << (19 + kShift)) + x;
+                own[t] = decltype(exact)::value && kk[t] == s;
             }
-            if (head == tail) break;
-            const uint32_t x = head + (uint32_t)lane;
-            head = min(head + 64u, tail);
-            if (x < tail) {
-                // ring entry: vertex | chunk index << 16 | live << 31
-                const uint32_t ent = ws.ring[x];
-                const int v = (int)(ent & 0xFFFFu);
-                const int p0 = (int)((ent >> 16) & 0x7FFFu) * CH;
-                const bool live = (ent >> 31) != 0u;
-                const int s = ws.S[v];
-                const uint32_t vi = gptr(I.vinfo)[v];
-                const auto cw = Chunk<CH>::colours(I.cand + (size_t)v * TS + p0);
-                uint32_t tv[CH];
-#pragma unroll
-                for (int t = 0; t < CH; ++t) tv[t] = 0u;
-                if (live) Chunk<CH>::tabu(tabu + (size_t)v * TS + p0, tv);
-                const int r = (int)(vi & 0xFFu), c = (int)((vi >> 8) & 0xFFu);
-                if (p0 == 0) lane_cands += (vi >> 16) & 0xFFu;
-                const uint8_t *rH = rowH + r * np1;
-                const uint8_t *cH = colH + c * np1;
-                const int32_t cur = s ? ((int32_t)rH[s] + (int32_t)cH[s] - 2) : 0;
-                // e = eB df + eA (conf(v,k) - cur), df = -1 when v was
-                // uncoloured, +1 for the uncolour move (k = 0, position 0)
-                const int32_t base = 0x8000 + (s ? 0 : -eB) - eA * cur;
-                const uint32_t hv = fmix32(w1 ^ (uint32_t)v) >> 16;
-                // winner payload: row, column, current colour, degree
-                const uint32_t vpay =
-                    (uint32_t)r | ((uint32_t)c << 8) | ((uint32_t)s << 16) | (vi & 0xFF000000u);
-                // all LDS reads of the chunk issued together
-                int kk[CH], cnt[CH];
-                uint32_t hkv[CH];
-#pragma unroll
-                for (int t = 0; t < CH; ++t) kk[t] = (int)((cw >> (8 * t)) & 0xFFu);
-#pragma unroll
-                for (int t = 0; t < CH; ++t) cnt[t] = (int)rH[kk[t]] + (int)cH[kk[t]];
-#pragma unroll
-                for (int t = 0; t < CH; ++t) hkv[t] = ws.hk[kk[t]];
-                bool took = false;
-#pragma unroll
-                for (int t = 0; t < CH; ++t) {
-                    const int k = kk[t];
-                    const int32_t b = (t == 0 && p0 == 0) ? base + eB : base;
-                    const int32_t eb = eA * cnt[t] + b;
-                    // positions past the domain repeat its last colour and
-                    // that colour's tabu entry: they never beat the original,
-                    // which this lane met first
-                    const bool ok = (k != s) && (itu >= tv[t] || eb < teb);
-                    const uint32_t hi = ((uint32_t)eb << 16) | (hv ^ hkv[t]);
-                    const bool take = ok && hi < lhi;
-                    lhi = take ? hi : lhi;
-                    lk = take ? (uint32_t)k : lk;
-                    took = took || take;
-                }
-                lv = took ? (uint32_t)v : lv;
-                lpay = took ? vpay : lpay;
+            if (g + kG < CH) {
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(g + kG);
             }
-            PLSE_WAVE_SYNC();
+            // keeps the compares of the expiries out of the branch that loads
+            // them, where their results would wait in scalar registers
+#pragma unroll
+            for (int t = 0; t < kG; ++t) asm volatile("" : "+v"(tv[g + t]));
+#pragma unroll
+            for (int t = 0; t < kG; ++t) {
+                // positions past the domain repeat its last colour and that
+                // colour's tabu entry: they never beat the original, which
+                // has a smaller position
+                const bool ok = !own[t] & ((itu >= tv[g + t]) | (key[t] < teb));
+                best = min(best, ok ? key[t] : 0xFFFFFFFFu);
+            }
+            if (g + kG < CH) __builtin_amdgcn_sched_barrier(0);
         }
-        // 3. unique best over the wave: minimum of the upper key words, then
-        //    of the move ids among the lanes holding it
-        const uint32_t ghi = wave_min_u32_dpp(lhi);
-        if (ghi == 0xFFFFFFFFu) {
-            ucnt.idle++;
-            continue;
-        }
-        // the move id of the lane holding the minimum (a second minimum over
-        // move ids only when several lanes share the upper word)
-        uint64_t who = ballot(lhi == ghi);
+        // positions ascend with colours: (value, tie value, id) of the
+        // chunk's best decides against another chunk
+        const uint32_t hi = best >> 3;
+        const uint32_t id = (v << 7) | colour_at(cw, best & 7u);
+        const bool take = hi < b.hi || (hi == b.hi && id < b.id);
+        b.hi = take ? hi : b.hi;
+        b.id = take ? id : b.id;
+        b.pay = take ? pay : b.pay;
+    };
+    // Unique best over the wave: minimum of value and tie value, then of the
+    // move ids among the lanes holding it; false: no admissible move.
+    auto choose = [&](const Best &b, uint32_t &id, uint32_t &pay) -> bool {
+        const uint32_t ghi = wave_min_u32_dpp(b.hi);
+        uint64_t who = ballot(b.hi == ghi);
         if (__popcll(who) != 1) {
-            const uint32_t lcid = lv * (uint32_t)np1 + lk;
-            const uint32_t glo = wave_min_u32_dpp(lhi == ghi ? lcid : 0xFFFFFFFFu);
-            who = ballot(lhi == ghi && lcid == glo);
+            const uint32_t gid = wave_min_u32_dpp(b.hi == ghi ? b.id : 0xFFFFFFFFu);
+            who = ballot(b.hi == ghi && b.id == gid);
         }
-        const int wl = (int)__ffsll((unsigned long long)who) - 1;
-        const uint32_t pay = readlane_u32(lpay, wl);
-        const int v = (int)readlane_u32(lv, wl);
-        const int k = (int)readlane_u32(lk, wl);
+        const int wl = (int)__builtin_ctzll(who);
+        id = readlane_u32(b.id, wl);
+        pay = readlane_u32(b.pay, wl);
+        return ghi != kNoMove;
+    };
+    // Apply move (v, k); with `keep`, also to the list.  False: the list could
+    // not take a vertex that joined.
+    auto apply = [&](auto keep, uint32_t id, uint32_t pay) -> bool {
+        bool list_ok = decltype(keep)::value;
+        const int v = (int)(id >> 7), k = (int)(id & 0x7Fu);
         const int r = (int)(pay & 0xFFu);
         const int c = (int)((pay >> 8) & 0xFFu);
         const int old = (int)((pay >> 16) & 0xFFu);
@@ -469,11 +538,13 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
         // domain mask (the tabu position of the colour it leaves)
         uint8_t *rH = rowH + r * np1;
         uint8_t *cH = colH + c * np1;
-        const int32_t hk_r = rH[k], hk_c = cH[k], ho_r = rH[old], ho_c = cH[old];
+        // (wave-uniform: the bookkeeping below stays in scalar registers)
+        const int32_t hk_r = readfirst(rH[k]), hk_c = readfirst(cH[k]);
+        const int32_t ho_r = readfirst(rH[old]), ho_c = readfirst(cH[old]);
         const uint32_t *nb = I.nbr + (size_t)v * I.nl;
         const uint32_t ent0 = lane < deg ? gptr(nb)[lane] : 0u;
         u32x4 dmask{0u, 0u, 0u, 0u};
-        if constexpr (PH != 3) dmask = gload4(reinterpret_cast<const u32x4 *>(I.vrec) + 2 * v);
+        if constexpr (PH != 3) dmask = *cptr(reinterpret_cast<const u32x4 *>(I.vrec) + 2 * v);
         const int32_t cvk = k ? hk_r + hk_c : 0;
         const int32_t cvo = old ? ho_r + ho_c - 2 : 0;
         const bool vC = (k != 0) && (cvk > 0);
@@ -494,8 +565,7 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                 atomicAdd(&ws.bm[v >> 5], 0u - (1u << (v & 31)));
             }
             sc.f += cvk - 1;
-            sc.F = sc.f;
-            ucnt.cupd += 2u + 2u * (uint32_t)cvk;
+            n_ends += 1u + (uint32_t)cvk;
             const uint32_t mp = (uint32_t)sc.f;
             const uint32_t T = scale32(w0, 10u) + udiv_by(alpha_n * mp, alpha_d, m_alpha);
             const uint32_t until = itu + 1u + T;
@@ -503,11 +573,19 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             // conflict-table entries: v's neighbours, then each uncoloured
             // vertex's neighbours
             uint32_t nupd_l = 0u;
+            if (list_ok) drop((uint32_t)v);
             for (int t0 = 0; t0 < deg; t0 += 64) {
                 const int t = t0 + lane;
                 const uint32_t ent = t0 == 0 ? ent0 : (t < deg ? gptr(nb)[t] : 0u);
                 const int u = (int)(ent & 0xFFFFu), other = (int)((ent >> 16) & 0x7FFFu);
-                if (t < deg && ws.S[u] == k) {
+                const bool freed = t < deg && ws.S[u] == k;
+                uint64_t joins = list_ok ? ballot(freed) : 0ull;
+                while (joins) {
+                    const int L = (int)__ffsll((unsigned long long)joins) - 1;
+                    joins &= joins - 1ull;
+                    list_ok = enlist(readlane_u32((uint32_t)u, L), 0u) && list_ok;
+                }
+                if (freed) {
                     nupd_l += gptr(I.vinfo)[u] >> 24;
                     const bool inrow = (ent >> 31) == 0;
                     const int ur = inrow ? r : other, uc = inrow ? other : c;
@@ -531,7 +609,7 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                     if (mark > ws.tm8[u]) ws.tm8[u] = (uint8_t)mark;
                 }
             }
-            ucnt.nupd += (uint64_t)deg + wave_sum_u32_dpp(nupd_l);
+            n_nupd += (uint32_t)deg + wave_sum_u32_dpp(nupd_l);
         } else {
             // 4. apply.  Counts: lanes 0-1 the leaving colour's row and column
             //    count (-1), lanes 2-3 the entering colour's (+1), as LDS adds on
@@ -554,6 +632,17 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             // eligibility of the row/column vertices holding the old or new colour:
             // all reads unconditional, one toggle where it changes
             int32_t dC = 0;
+            if constexpr (decltype(keep)::value) {
+                // v's chunks: its new colour, or free
+                const bool leaves = k != 0 && !vC;
+                const uint32_t npay = (pay & 0xFF00FFFFu) | ((uint32_t)k << 16);
+#pragma unroll
+                for (int q = 0; q < R; ++q) {
+                    const bool me = (sent[q] & 0xFFFFu) == (uint32_t)v;
+                    sent[q] = (me && leaves) ? kFreeLane : sent[q];
+                    spay[q] = me ? npay : spay[q];
+                }
+            }
             for (int t0 = 0; t0 < deg; t0 += 64) {
                 const int t = t0 + lane;
                 const uint32_t ent = t0 == 0 ? ent0 : (t < deg ? gptr(nb)[t] : 0u);
@@ -568,16 +657,28 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                 const bool now = cu > 0;
                 const bool flip = hit && (now != was);
                 if (flip) atomicXor(&ws.bm[u >> 5], 1u << (u & 31));
-                dC += (int32_t)__popcll(ballot(flip && now)) - (int32_t)__popcll(ballot(flip && !now));
+                uint64_t joins = ballot(flip && now), leaves = ballot(flip && !now);
+                dC += (int32_t)__popcll(joins) - (int32_t)__popcll(leaves);
+                if (list_ok) {
+                    while (leaves) {
+                        const int L = (int)__ffsll((unsigned long long)leaves) - 1;
+                        leaves &= leaves - 1ull;
+                        drop(readlane_u32((uint32_t)u, L));
+                    }
+                    while (joins) {
+                        const int L = (int)__ffsll((unsigned long long)joins) - 1;
+                        joins &= joins - 1ull;
+                        list_ok = enlist(readlane_u32((uint32_t)u, L), (uint32_t)k) && list_ok;
+                    }
+                }
             }
             const int32_t df = (k == 0 ? 1 : 0) - (old == 0 ? 1 : 0);
             sc.nC += dC + (vC ? 1 : 0) - (old ? 1 : 0);
             sc.f += df;
             sc.c += cvk - cvo;
-            sc.F += (int64_t)phi_den * df + (int64_t)phi_num * (cvk - cvo);
             const uint32_t ends = (uint32_t)(old != 0) + (uint32_t)(k != 0);
-            ucnt.cupd += 2u * ends;
-            ucnt.nupd += (uint32_t)deg * ends;
+            n_ends += ends;
+            n_nupd += (uint32_t)deg * ends;
             // tenure T = L + alpha (|V_0| + |C|) after the move; moving v back to
             // `old` is tabu for T iterations
             const uint32_t mp = (uint32_t)(sc.f + sc.nC);
@@ -598,14 +699,215 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             }
         }
         PLSE_WAVE_SYNC();
-        if (sc.F < sc.Fbest) {
-            sc.Fbest = sc.F;
+        // F < F*: in phase 2 the conflicts decide, except one conflict more
+        // against |V| uncoloured vertices fewer, which is equal
+        const int32_t gf = sc.f - sc.fbest, gc = sc.c - sc.cbest;
+        if (PH == 1 ? 2 * gf + gc < 0
+                    : (PH == 3 ? gf < 0 : (gc < -1 || (gc == -1 && gf < nv) || (gc == 0 && gf < 0)))) {
             sc.fbest = sc.f;
             sc.cbest = sc.c;
             snapshot(I, ws.S, out);
             ucnt.snaps++;
         }
+        return list_ok;
+    };
+    // Stage the eligible vertices of rank g .. g + kPlitsStage - 1, ascending.
+    auto stage_from = [&](uint32_t g) {
+        const int lane = rare_lane();
+        const uint32_t gend = g + (uint32_t)kPlitsStage;
+        uint32_t base = 0;
+        for (int wb = 0; wb < W && base < gend; wb += 64) {
+            const int w = wb + lane;
+            uint32_t bits = (w < W) ? ws.bm[w] : 0u;
+            uint32_t total;
+            uint32_t pos = base + wave_excl_scan_dpp((uint32_t)__popc(bits), &total);
+#pragma unroll 1
+            while (bits && pos < gend) {
+                const int b = __ffs(bits) - 1;
+                bits &= bits - 1u;
+                if (pos >= g) ws.stage[pos - g] = (uint16_t)(w * 32 + b);
+                ++pos;
+            }
+            base += total;
+        }
+        PLSE_WAVE_SYNC();
+    };
+    // Make the list of the staged eligible vertices; false if they do not fit.
+    auto build = [&]() -> bool {
+        const int lane = rare_lane();
+        const uint32_t m = eligible();
+        if (m > (uint32_t)kPlitsStage) return false;
+        stage_from(0u);
+#pragma unroll
+        for (int q = 0; q < R; ++q) sent[q] = kFreeLane, spay[q] = 0u, scw[q] = 0;
+        uint32_t chunks = 0u;
+        for (uint32_t g = 0u; g < m; g += 64u) {
+            const uint32_t e = g + (uint32_t)lane;
+            uint32_t v = 0u, nch = 0u, d = 0u;
+            if (e < m) {
+                v = ws.stage[e];
+                d = (*gptr(at_byte<uint32_t>(I.vinfo, v * 4u)) >> 16) & 0xFFu;
+                nch = d / CH + 1u;
+            }
+            uint32_t total;
+            const uint32_t at = wave_excl_scan_dpp(nch, &total);
+#pragma unroll 1
+            for (uint32_t t = 0; t < nch; ++t)
+                ws.ring[at + t] = v | (t << 16) | (t == 0u ? d << 24 : 0u);
+            PLSE_WAVE_SYNC();
+#pragma unroll
+            for (int q = 0; q < R; ++q) {
+                const uint32_t y = 64u * (uint32_t)q + (uint32_t)lane - chunks;
+                if (y < total) sent[q] = ws.ring[y];
+            }
+            PLSE_WAVE_SYNC();
+            chunks += total;
+        }
+        if (chunks > 64u * (uint32_t)R) return false;
+        slots = max(1u, (chunks + 63u) >> 6);
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            if (sent[q] != kFreeLane) {
+                const uint32_t v = sent[q] & 0xFFFFu, ci = (sent[q] >> 16) & 0xFFu;
+                const uint32_t vi = *gptr(at_byte<uint32_t>(I.vinfo, v * 4u));
+                spay[q] = (vi & 0xFF00FFFFu) | ((uint32_t)ws.S[v] << 16);
+                scw[q] = Chunk<CH>::colours(at_byte<uint8_t>(I.cand, v * (uint32_t)TS + ci * CH));
+            }
+        }
+        return true;
+    };
+
+    // One exit per loop: the list's registers then stay where they are.
+    bool done = end == 0u || eligible() == 0u, deal = true;
+    while (!done) {
+        if (deal) {
+            // dealt iterations, until the chunks fit the list
+            do {
+                begin();
+                stage_from(0u);
+                const uint32_t m = eligible();
+                n_elig += m;
+                const int lane = rare_lane();
+                const uint32_t teb = bound();
+                Best b{kNoMove, 0u, 0u};
+                uint32_t chunks = 0u;
+                uint32_t head = 0u, tail = 0u, g = 0u;
+                uint32_t sbase = 0u;  // rank of stage[0]
+                for (;;) {
+                    // once the ring is empty, deal the rows of the next 64 eligible
+                    // vertices into it
+                    if (head == tail && g < m) {
+                        head = tail = 0u;
+                        if (g >= sbase + (uint32_t)kPlitsStage) {
+                            // the bitmap does not change within the iteration
+                            PLSE_WAVE_SYNC();
+                            sbase = g;
+                            stage_from(g);
+                        }
+                        const uint32_t e = g + (uint32_t)lane;
+                        uint32_t v = 0u, nch = 0u, ent = 0u;
+                        if (e < m) {
+                            v = ws.stage[e - sbase];
+                            // chunk count and liveness of v, read together: planes 0
+                            // and 1 (or 0 twice), further planes only when present
+                            const int vw = (int)(v >> 5);
+                            const bool p0ok = ws.nplanes > 0, p1ok = ws.nplanes > 1;
+                            const uint32_t q0 = p0ok ? ws.planes[vw] : 0u;
+                            const uint32_t q1 = p1ok ? ws.planes[W + vw] : 0u;
+                            const uint32_t tm = ws.tm8[v];
+                            uint32_t code = ((q0 >> (v & 31u)) & 1u) | (((q1 >> (v & 31u)) & 1u) << 1);
+                            if (ws.nplanes > 2) {
+#pragma unroll
+                                for (int b = 2; b < 6; ++b)
+                                    if (b < ws.nplanes)
+                                        code |= ((ws.planes[b * W + vw] >> (v & 31u)) & 1u) << b;
+                            }
+                            nch = code + 1u;  // ceil((d + 1) / CH)
+                            // a vertex not live has no tabu move this iteration
+                            const bool live = tm > itu - tbase + 1u;
+                            ent = v | ((uint32_t)live << 31);
+                        }
+                        uint32_t total;
+                        const uint32_t at = tail + wave_excl_scan_dpp(nch, &total);
+#pragma unroll 1
+                        for (uint32_t t = 0; t < nch; ++t) ws.ring[at + t] = ent | (t << 16);
+                        tail += total;
+                        g += 64u;
+                        PLSE_WAVE_SYNC();
+                        chunks += total;
+                    }
+                    if (head == tail) break;
+                    const uint32_t x = head + (uint32_t)lane;
+                    head = min(head + 64u, tail);
+                    if (x < tail) {
+                        // ring entry: vertex | chunk index << 16 | live << 31
+                        const uint32_t ent = ws.ring[x];
+                        const uint32_t v = ent & 0xFFFFu, ci = (ent >> 16) & 0x7FFFu;
+                        const uint32_t vi = *gptr(at_byte<uint32_t>(I.vinfo, v * 4u));
+                        if (ci == 0u) lane_cands += (vi >> 16) & 0xFFu;
+                        look(std::true_type{}, b, teb, v, ci, (ent >> 31) != 0u, (vi & 0xFF00FFFFu) | ((uint32_t)ws.S[v] << 16),
+                             Chunk<CH>::colours(at_byte<uint8_t>(I.cand, v * (uint32_t)TS + ci * CH)));
+                    }
+                    PLSE_WAVE_SYNC();
+                }
+                uint32_t id, pay;
+                if (choose(b, id, pay))
+                    (void)apply(std::false_type{}, id, pay);
+                else
+                    ucnt.idle++;
+                ++itu;
+                done = itu >= end || eligible() == 0u;  // none: complete legal colouring
+                deal = chunks + 32u > 64u * (uint32_t)R;
+            } while (deal && !done);
+        }
+        if (!done) {
+            deal = !build();
+            if (!deal) {
+                // iterations on the list
+                bool relist = false;
+                do {
+                    begin();
+                    const uint32_t m = eligible(), teb = bound(), cands0 = lane_cands;
+                    Best b{kNoMove, 0u, 0u};
+#pragma unroll
+                    for (int q = 0; q < R; ++q) {
+                        if ((uint32_t)q >= slots) break;
+                        if (sent[q] != kFreeLane) {
+                            const uint32_t v = sent[q] & 0xFFFFu;
+                            const uint32_t tm = ws.tm8[v];
+                            lane_cands += sent[q] >> 24;
+                            look(std::false_type{}, b, teb, v, (sent[q] >> 16) & 0xFFu,
+                                 tm > itu - tbase + 1u, spay[q], scw[q]);
+                        }
+                    }
+                    PLSE_WAVE_SYNC();
+                    uint32_t id, pay;
+                    const bool any = choose(b, id, pay);
+                    // nothing is better than a vertex's own colour: such moves
+                    // have to be told apart, which the dealt form does
+                    const bool own = any && (id & 0x7Fu) == ((pay >> 16) & 0xFFu);
+                    bool room = true;
+                    if (any && !own) room = apply(std::true_type{}, id, pay);
+                    ucnt.idle += any ? 0u : 1u;
+                    n_elig += own ? 0u : m;
+                    itu += own ? 0u : 1u;
+                    lane_cands = own ? cands0 : lane_cands;
+                    if ((itu & 15u) == 0u && slots > 1u) {
+                        // fewer chunks than the slots in use are there for
+                        uint32_t chunks = 0u;
+#pragma unroll
+                        for (int q = 0; q < R; ++q)
+                            chunks += (uint32_t)__popcll(ballot(sent[q] != kFreeLane));
+                        relist = chunks + 8u <= 64u * (slots - 1u);
+                    }
+                    deal = own || !room;
+                    done = itu >= end || eligible() == 0u;
+                } while (!deal && !relist && !done);
+            }
+        }
     }
+    ucnt.iters += itu;
+    tally();
     // the last move's tabu entry and mark: the mark tells clear_tabu the row
     // was written
     if (pend_off != 0xFFFFFFFFu) gptr(tabu)[pend_off] = pend_val;
@@ -620,7 +922,7 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
 __device__ void repair(const PlitsArgs &a, const uint8_t *from, uint8_t *out, const WaveState &ws,
                        Scal &sc, Cnt &ucnt) {
     const DevInstance &I = a.I;
-    const int lane = lane_id();
+    const int lane = rare_lane();
     const int n = I.n, nv = I.nv, np1 = n + 1;
     setup_state(I, from, ws, sc);
     uint8_t *rowH = ws.H, *colH = ws.H + n * np1;
@@ -666,7 +968,7 @@ __device__ __forceinline__ void plits_individual(const PlitsArgs &a, int ind, in
     ws.tm8 = base + a.off_tm;
     ws.stage = reinterpret_cast<uint16_t *>(base + a.off_el);
     ws.ring = reinterpret_cast<uint32_t *>(base + a.off_ring);
-    ws.hk = reinterpret_cast<uint16_t *>(base + a.off_hk);
+    ws.hk = reinterpret_cast<uint32_t *>(base + a.off_hk);
     ws.planes = reinterpret_cast<uint32_t *>(base + a.off_planes);
     ws.nplanes = a.nplanes;
     {
@@ -684,6 +986,7 @@ __device__ __forceinline__ void plits_individual(const PlitsArgs &a, int ind, in
         }
     }
     const DevInstance &I = a.I;
+    ind = readfirst(ind);
     uint32_t *tabu = a.tabu + (size_t)ind * I.nv * I.ts;
     const uint8_t *src = a.S_in + (size_t)ind * I.stride;
     uint8_t *out = a.S_out + (size_t)ind * I.stride;
@@ -691,7 +994,7 @@ __device__ __forceinline__ void plits_individual(const PlitsArgs &a, int ind, in
     Cnt ucnt{0u, 0u, 0u, 0u, 0ull, 0ull, 0ull};
     uint32_t lane_cands = 0;
     Scal sc;
-    const uint32_t slot = (uint32_t)readfirst(ind);
+    const uint32_t slot = (uint32_t)ind;
     int32_t f_final;
     if constexpr (PARTIAL) {
         // Partial-MPMA (Section 3.7): the offspring repaired into a legal
@@ -738,9 +1041,7 @@ __device__ __forceinline__ void plits_individual(const PlitsArgs &a, int ind, in
 template <int CH, bool PARTIAL>
 __global__ __launch_bounds__(256, 4) void plits_kernel(const ArgList L) {
     extern __shared__ __align__(16) uint8_t lds[];
-    // by reference: fields needed only before or after a phase are read when
-    // needed instead of being held in registers through the search
-    const PlitsArgs &a = *static_cast<const PlitsArgs *>(L.p[blockIdx.y]);
+    const PlitsArgs a = cload<PlitsArgs>(L.p[blockIdx.y]);
     const int wv = (int)(threadIdx.x >> 6);
     const int ind = (int)blockIdx.x * (int)(blockDim.x >> 6) + wv;
     if (ind >= a.p) return;
@@ -770,7 +1071,7 @@ __global__ __launch_bounds__(256, 4) void plits_persistent_kernel(const ArgList 
         item = readlane_u32(item, 0);
         if (item >= total) break;
         const uint32_t inst = item / (uint32_t)p, ind = item - inst * (uint32_t)p;
-        const PlitsArgs &a = *static_cast<const PlitsArgs *>(L.p[inst]);
+        const PlitsArgs a = cload<PlitsArgs>(L.p[inst]);
         int gen = a.gen_fixed;
         if (gen == 0) {
             if (gptr(a.ctl)->stop) continue;

@@ -932,3 +932,59 @@ def test_select_row_lengths(torch_cuda, oracle_mod, p, spacing):
                          2, p)
     torch.cuda.synchronize()
     np.testing.assert_array_equal(_np(acc), oracle_mod.select(nv, p, spacing, p, 2, f, D))
+
+
+# --- tabu search: the chunk list ------------------------------------------------------------
+def _holes(n, cells):
+    """A cyclic Latin square of order n with the given cells emptied."""
+    g = ((np.arange(n)[:, None] + np.arange(n)[None, :]) % n + 1).astype(np.int8)
+    for r, c in cells:
+        g[r, c] = 0
+    return g
+
+
+@pytest.mark.parametrize("name,p,depth,spl,alpha,variant", [
+    ("two", 8, 300, 8, 0, 0),          # one, two and three vertices: the value scale's limits
+    ("three", 8, 300, 8, 0, 0),
+    ("corner", 8, 300, 4, 0, 0),
+    ("small", 16, 2000, 8, 40, 0),     # tenures beyond the phase: every move tabu, idle
+    ("small", 16, 2000, 2, 40, 0),     # iterations, own colours as the best "move"
+    ("small", 16, 2000, 4, 40, 1),
+    ("empty14", 9, 3000, 2, 0, 0),     # up to eight chunks a vertex: around the list's capacity
+    ("empty14", 9, 3000, 4, 0, 1),
+    ("wide", 6, 2500, 8, 0, 0),        # 64-colour rows: n at the widths of the tie values
+    ("wide", 6, 2500, 4, 0, 1),
+])
+def test_plits_chunk_list(torch_cuda, oracle_mod, name, p, depth, spl, alpha, variant):
+    """Searches that enter and leave the list form of the iterations (random
+    conflicting starts descend in the dealt form), with vertices of several
+    chunks, lists near and beyond capacity, iterations without an admissible
+    move, and the smallest instances: S', f' and every counter equal the
+    oracle's."""
+    g = {"two": lambda: _holes(5, [(1, 1), (1, 3)]),
+         "three": lambda: _holes(5, [(1, 1), (1, 3), (2, 1)]),
+         "corner": lambda: _holes(4, [(0, 0)]),
+         "small": lambda: gen.planted(8, 0.6, 3),
+         "empty14": lambda: np.zeros((14, 14), dtype=np.int8),
+         "wide": lambda: gen.planted(64, 0.8, 5)}[name]()
+    _say(f"plits list {name} p={p} depth={depth} spl={spl} alpha={alpha} variant={variant}")
+    kw = dict(alpha_num=alpha, alpha_den=1) if alpha else {}
+    s = P.Solver(g, depth=depth, slots_per_lane=spl, variant=variant, plits_kernel=1, **kw)
+    I = oracle_mod.Instance(g)
+    vr, vc, off, dom = I.tables()
+    rng = np.random.default_rng(17)
+    S0 = np.zeros((p, s.stride), dtype=np.uint8)
+    for i in range(p):
+        for v in range(I.nv):
+            choices = [0] + list(dom[off[v]:off[v + 1]])
+            S0[i, v] = choices[rng.integers(0, len(choices))]
+    import torch
+    S1, f1, c1 = s.stage_plits(torch.from_numpy(S0).cuda(), 5, 1234)
+    torch.cuda.synchronize()
+    Po = I.params(depth=depth, variant=oracle_mod.V_PARTIAL) if variant else I.params(depth=depth)
+    if alpha:
+        Po[oracle_mod.P_ALPHA_NUM], Po[oracle_mod.P_ALPHA_DEN] = alpha, 1
+    S1o, f1o, c1o = I.plits(Po, 1234, 5, list(range(p)), S0[:, :I.nv])
+    np.testing.assert_array_equal(_np(S1)[:, :I.nv], S1o)
+    np.testing.assert_array_equal(_np(f1), f1o)
+    np.testing.assert_array_equal(_np(c1).astype(np.uint64), c1o)
