@@ -332,9 +332,9 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
     // the next iteration (under the eligibility scan)
     uint32_t pend_tv = 0xFFFFFFFFu, pend_tu = 0u;
     uint32_t tbase = 0u;  // base of the relative expiry marks
-    // lane roles of the count updates (all ones / all zeros)
-    const uint32_t ln_new = lane >= 2 ? 0xFFFFFFFFu : 0u;  // entering colour
-    const uint32_t ln_odd = (lane & 1) ? 0xFFFFFFFFu : 0u;  // column count
+    // lane roles of the count updates
+    const bool ln_new = (lane & 2) != 0;  // entering colour
+    const bool ln_odd = (lane & 1) != 0;  // column count
     PLSE_WAVE_SYNC();
 
     // The chunk list: one chunk per lane and slot (vertex | chunk << 16 and, in
@@ -433,6 +433,11 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                          : (PH == 1 ? 2 * (sc.fbest - sc.f) + (sc.cbest - sc.c) : sc.fbest - sc.f);
         return (uint32_t)max(te + kZeroMove, 0) << 19;
     };
+    // Wave-uniform flags as 0 or 1 in scalar registers (as conditions they
+    // would be kept as lane masks); the 1 is opaque, or min became a compare.
+    uint32_t one = 1u;
+    asm("" : "+s"(one));
+    auto nonzero = [&](uint32_t x) -> uint32_t { return min(x, one); };
     auto eligible = [&]() -> uint32_t { return (uint32_t)(PH == 3 ? sc.f : sc.f + sc.nC); };
     // The best move of chunk ci of vertex v (pay: row | column << 8 |
     // colour << 16 | degree << 24) against the lane's best so far.  Without
@@ -511,8 +516,8 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
         b.pay = take ? pay : b.pay;
     };
     // Unique best over the wave: minimum of value and tie value, then of the
-    // move ids among the lanes holding it; false: no admissible move.
-    auto choose = [&](const Best &b, uint32_t &id, uint32_t &pay) -> bool {
+    // move ids among the lanes holding it; 0: no admissible move.
+    auto choose = [&](const Best &b, uint32_t &id, uint32_t &pay) -> uint32_t {
         const uint32_t ghi = wave_min_u32_dpp(b.hi);
         uint64_t who = ballot(b.hi == ghi);
         if (__popcll(who) != 1) {
@@ -522,7 +527,7 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
         const int wl = (int)__builtin_ctzll(who);
         id = readlane_u32(b.id, wl);
         pay = readlane_u32(b.pay, wl);
-        return ghi != kNoMove;
+        return nonzero(ghi ^ kNoMove);
     };
     // Apply move (v, k); with `keep`, also to the list.  False: the list could
     // not take a vertex that joined.
@@ -536,28 +541,29 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
         // the counts of the two colours in v's row and column, then the memory
         // the apply needs, fetched together: v's first 64 neighbours and its
         // domain mask (the tabu position of the colour it leaves)
-        uint8_t *rH = rowH + r * np1;
-        uint8_t *cH = colH + c * np1;
-        // (wave-uniform: the bookkeeping below stays in scalar registers)
-        const int32_t hk_r = readfirst(rH[k]), hk_c = readfirst(cH[k]);
-        const int32_t ho_r = readfirst(rH[old]), ho_c = readfirst(cH[old]);
+        // (read through one address per lane: 0-1 old's row and column count,
+        // 2-3 k's, where the move's updates go too)
+        const uint32_t hcol = (uint32_t)(ln_new ? k : old);
+        const uint32_t hb = (uint32_t)(ln_odd ? (n + c) * np1 : r * np1) + hcol;
+        const uint32_t hval = ws.H[hb];
+        const int32_t ho_r = (int32_t)readlane_u32(hval, 0), ho_c = (int32_t)readlane_u32(hval, 1);
+        const int32_t hk_r = (int32_t)readlane_u32(hval, 2), hk_c = (int32_t)readlane_u32(hval, 3);
         const uint32_t *nb = I.nbr + (size_t)v * I.nl;
         const uint32_t ent0 = lane < deg ? gptr(nb)[lane] : 0u;
         u32x4 dmask{0u, 0u, 0u, 0u};
         if constexpr (PH != 3) dmask = *cptr(reinterpret_cast<const u32x4 *>(I.vrec) + 2 * v);
         const int32_t cvk = k ? hk_r + hk_c : 0;
         const int32_t cvo = old ? ho_r + ho_c - 2 : 0;
-        const bool vC = (k != 0) && (cvk > 0);
+        const uint32_t is_k = nonzero((uint32_t)k), is_old = nonzero((uint32_t)old);
+        const uint32_t vC = nonzero((uint32_t)cvk);  // v in conflict
+        const uint32_t stays = vC | (1u ^ is_k);      // v in V_0 u C(S)
         PLSE_WAVE_SYNC();
         if constexpr (PH == 3) {
             // PartialCol: v (uncoloured) takes k; its cvk neighbours holding k
             // (at most one per row and column) are uncoloured and may not take
             // k back before `until`
             if (lane < 4) {
-                const uint32_t col = (ln_new & (uint32_t)k) | (~ln_new & (uint32_t)old);
-                const uint32_t hb = ((ln_odd & (uint32_t)(cH - ws.H)) |
-                                     (~ln_odd & (uint32_t)(rH - ws.H))) + col;
-                const uint32_t add = col != 0u ? ((ln_new & 2u) - 1u) << ((hb & 3u) * 8u) : 0u;
+                const uint32_t add = hcol != 0u ? (ln_new ? 1u : ~0u) << ((hb & 3u) * 8u) : 0u;
                 atomicAdd(reinterpret_cast<uint32_t *>(ws.H) + (hb >> 2), add);
             }
             if (lane == 0) {
@@ -616,17 +622,14 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             //    the bytes of u32 words (exact: counts stay within 0..n, nothing
             //    carries), an add of 0 for colour 0.  Lane 0: v's colour, and v's
             //    eligibility bit cleared (an exact add: v was eligible) unless v
-            //    stays in V_0 u C.  Lane roles are bit masks, not branches.
+            //    stays in V_0 u C.
             if (lane < 4) {
-                const uint32_t col = (ln_new & (uint32_t)k) | (~ln_new & (uint32_t)old);
-                const uint32_t hb = ((ln_odd & (uint32_t)(cH - ws.H)) |
-                                     (~ln_odd & (uint32_t)(rH - ws.H))) + col;
-                const uint32_t add = col != 0u ? ((ln_new & 2u) - 1u) << ((hb & 3u) * 8u) : 0u;
+                const uint32_t add = hcol != 0u ? (ln_new ? 1u : ~0u) << ((hb & 3u) * 8u) : 0u;
                 atomicAdd(reinterpret_cast<uint32_t *>(ws.H) + (hb >> 2), add);
             }
             if (lane == 0) {
                 ws.S[v] = (uint8_t)k;
-                atomicAdd(&ws.bm[v >> 5], (k == 0 || vC) ? 0u : 0u - (1u << (v & 31)));
+                atomicAdd(&ws.bm[v >> 5], (stays - 1u) & (0u - (1u << (v & 31))));
             }
             PLSE_WAVE_SYNC();
             // eligibility of the row/column vertices holding the old or new colour:
@@ -634,27 +637,31 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
             int32_t dC = 0;
             if constexpr (decltype(keep)::value) {
                 // v's chunks: its new colour, or free
-                const bool leaves = k != 0 && !vC;
-                const uint32_t npay = (pay & 0xFF00FFFFu) | ((uint32_t)k << 16);
+                if (stays) {
+                    const uint32_t npay = (pay & 0xFF00FFFFu) | ((uint32_t)k << 16);
 #pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const bool me = (sent[q] & 0xFFFFu) == (uint32_t)v;
-                    sent[q] = (me && leaves) ? kFreeLane : sent[q];
-                    spay[q] = me ? npay : spay[q];
+                    for (int q = 0; q < R; ++q)
+                        spay[q] = (sent[q] & 0xFFFFu) == (uint32_t)v ? npay : spay[q];
+                } else {
+                    drop((uint32_t)v);
                 }
             }
+            // those that hold k are in conflict now; those that hold old stay
+            // so unless it was with v alone: the count of the shared line
+            // without v is known, that of their other line read
+            const uint32_t kx = k ? (uint32_t)k : 256u, ox = old ? (uint32_t)old : 256u;
             for (int t0 = 0; t0 < deg; t0 += 64) {
                 const int t = t0 + lane;
                 const uint32_t ent = t0 == 0 ? ent0 : (t < deg ? gptr(nb)[t] : 0u);
                 const bool inrow = (ent >> 31) == 0;
                 const int u = (int)(ent & 0xFFFFu), other = (int)((ent >> 16) & 0x7FFFu);
-                const int su = ws.S[u];
+                const uint32_t su = ws.S[u];
                 const uint32_t bw = ws.bm[u >> 5];
-                const int rrow = inrow ? r : other, rcol = inrow ? other : c;
-                const int cu = (int)rowH[rrow * np1 + su] + (int)colH[rcol * np1 + su] - 2;
-                const bool hit = t < deg && su != 0 && (su == old || su == k);
+                const uint32_t other_n = ws.H[(other + (inrow ? n : 0)) * np1 + (int)su];
+                const uint32_t shared = (uint32_t)(inrow ? ho_r : ho_c);
+                const bool hit = (t < deg) & ((su == ox) | (su == kx));
                 const bool was = (bw >> (u & 31)) & 1u;
-                const bool now = cu > 0;
+                const bool now = (su == kx) | (shared + other_n > 3u);
                 const bool flip = hit && (now != was);
                 if (flip) atomicXor(&ws.bm[u >> 5], 1u << (u & 31));
                 uint64_t joins = ballot(flip && now), leaves = ballot(flip && !now);
@@ -672,11 +679,10 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                     }
                 }
             }
-            const int32_t df = (k == 0 ? 1 : 0) - (old == 0 ? 1 : 0);
-            sc.nC += dC + (vC ? 1 : 0) - (old ? 1 : 0);
-            sc.f += df;
+            sc.nC += dC + (int32_t)vC - (int32_t)is_old;
+            sc.f += (int32_t)is_old - (int32_t)is_k;
             sc.c += cvk - cvo;
-            const uint32_t ends = (uint32_t)(old != 0) + (uint32_t)(k != 0);
+            const uint32_t ends = is_old + is_k;
             n_ends += ends;
             n_nupd += (uint32_t)deg * ends;
             // tenure T = L + alpha (|V_0| + |C|) after the move; moving v back to
@@ -882,16 +888,16 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                     }
                     PLSE_WAVE_SYNC();
                     uint32_t id, pay;
-                    const bool any = choose(b, id, pay);
+                    const uint32_t any = choose(b, id, pay);
                     // nothing is better than a vertex's own colour: such moves
                     // have to be told apart, which the dealt form does
-                    const bool own = any && (id & 0x7Fu) == ((pay >> 16) & 0xFFu);
+                    const uint32_t own = any & (1u ^ nonzero((id & 0x7Fu) ^ ((pay >> 16) & 0xFFu)));
                     bool room = true;
-                    if (any && !own) room = apply(std::true_type{}, id, pay);
-                    ucnt.idle += any ? 0u : 1u;
-                    n_elig += own ? 0u : m;
-                    itu += own ? 0u : 1u;
-                    lane_cands = own ? cands0 : lane_cands;
+                    if (any > own) room = apply(std::true_type{}, id, pay);
+                    ucnt.idle += 1u ^ any;
+                    n_elig += m & (own - 1u);
+                    itu += 1u - own;
+                    if (own) lane_cands = cands0;
                     if ((itu & 15u) == 0u && slots > 1u) {
                         // fewer chunks than the slots in use are there for
                         uint32_t chunks = 0u;
