@@ -171,19 +171,25 @@ void set_attributes_once() {
 
 int max_lds_per_block() { return g_lds_limit; }
 
-// Candidate positions per lane and round in PLITS: the chunk size CH that
-// minimises the modelled evaluation work of one pass over every candidate
-// row, sum_v ceil((d_v + 1) / CH) (CH + 3), the 3 standing for a chunk's
-// fixed work (descriptor, vertex state, loads) in units of one move (fitted
-// to measured runs: with 1.5 the model picked 4 for the 70x70 grid 70 %
-// prefilled, which runs 7 % faster with 8).
+// Candidate positions per lane in PLITS: the chunk size CH that minimises the
+// modelled work of an iteration.  Its eligible vertices, 8 + |V| / 8 (6 to 22 at
+// orders 8 to 30, 24 of 1250 at n = 50, half prefilled, 145 of 1470 at n = 70,
+// 70 %), have chunks for at least one pass of 64 lanes, and a pass costs CH
+// moves plus 4.5 of their like for a chunk's fixed part.  So the smallest
+// instances, where one pass is the least there is, take chunks of 2 or 4: n = 10,
+// 40 %: 1.78 us an iteration of a lone search, 2.00 with 8; n = 16, 40 %: 1.81
+// with 4, 1.98 with 8; from n = 30 on few passes of 8 are better (n = 70, 70 %:
+// 2.7 ns an iteration over the device with 8, 3.3 with 4), except where domains
+// are small (n = 70, 80 %, PartialCol: 1.67 with 4, 1.96 with 8).
 int choose_spl(const plse_instance *h) {
     if (h->spl) return h->spl;
     int pick = 4;
     double best = 0.0;
     for (int ch : {2, 4, 8}) {
-        double cost = 0.0;
-        for (int v = 0; v < h->nv; ++v) cost += (double)((((h->vinfo[v] >> 16) & 0xFFu) + ch) / ch) * (ch + 3.0);
+        double chunks = 0.0;
+        for (int v = 0; v < h->nv; ++v) chunks += (double)((((h->vinfo[v] >> 16) & 0xFFu) + ch) / ch);
+        const double per_vertex = h->nv ? chunks / h->nv : 0.0;
+        const double cost = std::max(64.0, (8.0 + h->nv / 8.0) * per_vertex) * (ch + 4.5);
         if (ch == 2 || cost < best) {
             best = cost;
             pick = ch;

@@ -29,8 +29,11 @@
 //   Dealt: while the chunks do not fit (the first descent from an offspring,
 //   mostly), they are dealt to the lanes round by round from the eligibility
 //   bitmap, which both forms keep.
-//   Chunks of 8 in four slots hold 96 % of the iterations at n = 50, half
-//   prefilled (24 eligible vertices of 13 colours), and at n = 70, 70 %.
+//   Six slots hold the chunks in 97 % of the iterations at n = 50, half
+//   prefilled (24 eligible vertices of 13 colours).  With four, 22 % of the
+//   iterations at n = 70, 70 % (145 vertices of 6), and 34 % at n = 61, 65 %
+//   were dealt: 2.93 -> 2.72 ns an iteration there, 5.58 -> 5.17 us; eight gain
+//   no more and leave no registers over.
 //
 // Per wave (LDS): S[stride] colours, rowcnt|colcnt, the eligibility bitmap of
 //   V_0 u C(S), tm8[|V|] (per vertex: whether this phase wrote its tabu row,
@@ -57,14 +60,14 @@
 //
 // Bound by instruction issue: a lone wave takes about 7 cycles an instruction
 // of any kind, and 16 waves per CU keep the VALU busy for two thirds of the
-// time.  Per iteration at n = 50, half prefilled, |P| = 4096: 410 VALU, 294
-// scalar, 57 LDS instructions and 40 branches; with every iteration dealt 502,
+// time.  Per iteration at n = 50, half prefilled, |P| = 4096: 387 VALU, 279
+// scalar, 53 LDS instructions and 41 branches; with every iteration dealt 502,
 // 273, 68 and 55.  ns per iteration over the device (4096 searches) and us per
-// iteration of a lone search, dealt -> listed:
-//   n = 50, 50 % prefilled: 1.31 -> 1.21 ns, 2.74 -> 2.33 us
-//   n = 70, 70 %:           4.06 -> 3.18 ns, 6.38 -> 4.75 us
-//   n = 70, 80 %, PartialCol (chunks of 4): 2.94 -> 1.74 ns
-//   n = 100, 50 %:          8.72 -> 7.59 us;   n = 10: 2.58 -> 2.0 us
+// iteration of a lone search, all dealt -> now:
+//   n = 50, 50 % prefilled: 1.31 -> 1.15 ns, 2.74 -> 2.23 us
+//   n = 70, 70 %:           4.06 -> 2.72 ns, 6.38 -> 4.31 us
+//   n = 70, 80 %, PartialCol (chunks of 4): 2.94 -> 1.67 ns
+//   n = 100, 50 %:          8.72 -> 7.45 us;   n = 10: 2.58 -> 1.78 us
 // What keeps the scalar side small: wave-uniform values are made uniform for
 // the compiler (readfirst, scalar loads of arguments and tables), and each loop
 // has one exit, so that the list's registers are not copied at its joins.
@@ -243,7 +246,7 @@ struct Chunk<8> {
 };
 
 // Slots of the chunk list, and the mark of a free lane (no vertex has it).
-constexpr int kPlitsSlots = 4;
+constexpr int kPlitsSlots = 6;
 constexpr uint32_t kFreeLane = 0xFFFFFFFFu;
 constexpr int32_t kZeroMove = 0x1000;       // e of a move that changes nothing
 constexpr int32_t kOwnUncoloured = 0x1FFF;  // above every move's
