@@ -366,14 +366,20 @@ DevInstance dev_instance(plse_instance *h) {
     return I;
 }
 
-int upload_instance(plse_instance *h, hipStream_t s) {
+// Instance tables that a call's kernels read: none (rows of colours, distances
+// and draws only), those of the initial population, or all.
+enum class Tables { none, init, all };
+
+int upload_instance(plse_instance *h, hipStream_t s, Tables which = Tables::all) {
     const Layout &L = h->L;
     auto put = [&](size_t off, const void *src, size_t bytes) -> hipError_t {
         if (!bytes) return hipSuccess;
         return hipMemcpyAsync(h->ws + off, src, bytes, hipMemcpyHostToDevice, s);
     };
+    if (which == Tables::none) return PLSE_OK;
     HIP_TRY(put(L.vrc, h->vrc.data(), 2 * h->vrc.size()));
     HIP_TRY(put(L.vrec, h->vrec.data(), 4 * h->vrec.size()));
+    if (which == Tables::init) return PLSE_OK;
     HIP_TRY(put(L.cand, h->cand.data(), h->cand.size()));
     HIP_TRY(put(L.vinfo, h->vinfo.data(), 4 * h->vinfo.size()));
     HIP_TRY(put(L.nbr, h->nbr.data(), 4 * h->nbr.size()));
@@ -983,11 +989,14 @@ void drop_session(plse_instance *h) {
     h->in_session = false;
 }
 
-// Stage calls: one instance, argument block prepared on the host.
-int stage_prepare(plse_instance *h, int p, hipStream_t s) {
+// Stage calls: one instance, argument block prepared on the host.  Each call
+// uploads the tables that its kernels read (the workspace is the caller's, who
+// may have written it since): 16384 matched and crossed over at n = 50 need
+// none, and their seven copies took 100 us of 300.
+int stage_prepare(plse_instance *h, int p, hipStream_t s, Tables tables) {
     if (h->in_session) return PLSE_E_BUSY;
     RC_TRY(check_ws(h, p));
-    RC_TRY(upload_instance(h, s));
+    RC_TRY(upload_instance(h, s, tables));
     return PLSE_OK;
 }
 
@@ -1742,7 +1751,7 @@ int plse_stage_init(plse_handle h, int32_t p, uint64_t seed, void *stream, uint8
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, p, s));
+    RC_TRY(stage_prepare(h, p, s, Tables::init));
     h->args.init = InitArgs{dev_instance(h), S, f, p, init_log2_buckets(h->nv),
                             (uint32_t)seed, (uint32_t)(seed >> 32)};
     RC_TRY(upload_args(h, s));
@@ -1759,7 +1768,7 @@ int plse_stage_plits(plse_handle h, int32_t p, int32_t gen, uint64_t seed, void 
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, p, s));
+    RC_TRY(stage_prepare(h, p, s, Tables::all));
     h->args.plits = make_plits(h, p, gen, seed, S_in, S_out, f_out, counters, nullptr);
     h->args.fill = FillArgs{at<uint32_t>(h, h->L.tabu), (size_t)p * h->nv * h->ts};
     RC_TRY(upload_args(h, s));
@@ -1781,7 +1790,7 @@ namespace {
 // also 1, 2, 4 waves per block) and keeps the fastest on the handle.
 int autotune(plse_instance *h, int32_t sample, int32_t depth, uint64_t seed, hipStream_t s,
              bool waves, float *out_ms) {
-    RC_TRY(stage_prepare(h, sample, s));
+    RC_TRY(stage_prepare(h, sample, s, Tables::all));
     // the workspace's offspring, scratch and counter regions hold the sample
     uint8_t *S_in = at<uint8_t>(h, h->L.S_off), *S_out = at<uint8_t>(h, h->L.S_tmp);
     int32_t *f = at<int32_t>(h, h->L.f_tmp);
@@ -1878,7 +1887,7 @@ int plse_stage_distances(plse_handle h, int32_t m, void *stream, const uint8_t *
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, std::max(2, (m + 1) / 2), s));
+    RC_TRY(stage_prepare(h, std::max(2, (m + 1) / 2), s, Tables::none));
     const int W = (h->nv + 31) / 32, B = colour_bits(h->n);
     h->args.pack = PackArgs{nullptr, S, at<uint32_t>(h, h->L.planes), m, h->nv, h->stride, W, B, 0};
     const int nt1 = (m + kDistTile - 1) / kDistTile;
@@ -1895,7 +1904,7 @@ int plse_stage_select(plse_handle h, int32_t p, int32_t gen, uint64_t seed, void
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, p, s));
+    RC_TRY(stage_prepare(h, p, s, Tables::none));
     const int m = 2 * p;
     h->args.close = CloseArgs{nullptr, D_all, at<int32_t>(h, h->L.deg), at<uint16_t>(h, h->L.adj),
                               m, m, h->nv, h->P.spacing};
@@ -1914,7 +1923,7 @@ int plse_stage_match(plse_handle h, int32_t p, void *stream, const int16_t *D,
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, p, s));
+    RC_TRY(stage_prepare(h, p, s, Tables::none));
     const Layout &L = h->L;
     h->args.hash = HashArgs{nullptr, uid, at<uint64_t>(h, L.hkeys), at<int32_t>(h, L.hvals), p,
                             L.hsize};
@@ -1935,7 +1944,7 @@ int plse_stage_aux(plse_handle h, int32_t p, int32_t gen, uint64_t seed, void *s
     BusyGuard guard(h);
     if (!guard.ok) return PLSE_E_BUSY;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
-    RC_TRY(stage_prepare(h, p, s));
+    RC_TRY(stage_prepare(h, p, s, Tables::none));
     h->args.aux = AuxArgs{nullptr, S, partner, dpart, S_off, p, h->nv, h->stride, gen,
                           h->P.crossover, h->P.beta_num, h->P.beta_den, (uint32_t)seed,
                           (uint32_t)(seed >> 32)};
