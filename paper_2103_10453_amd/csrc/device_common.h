@@ -100,6 +100,13 @@ __device__ __forceinline__ __attribute__((address_space(1))) T *gptr(T *p) {
     return (__attribute__((address_space(1))) T *)p;
 }
 
+// Tables at wave-uniform addresses that no kernel running beside writes: scalar
+// loads.
+template <typename T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T *cptr(const T *p) {
+    return (const __attribute__((address_space(4))) T *)p;
+}
+
 // 8- and 16-byte global accesses (clang vector types: HIP's uint2/uint4
 // classes only bind to generic-address references).
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
@@ -110,9 +117,12 @@ __device__ __forceinline__ u32x4 gload4(const void *p) {
 __device__ __forceinline__ u32x2 gload2(const void *p) {
     return *gptr(reinterpret_cast<const u32x2 *>(p));
 }
-// 16 bytes from an address of any alignment: rows of 16-bit distances of odd
-// length (global loads need none on gfx950, and the compiler knows).
-typedef u32x4 u32x4_any __attribute__((aligned(2)));
+// Accesses at an address of any alignment: rows of 16-bit distances of odd
+// length, a caller's rows of bytes (global memory needs none on gfx950, and the
+// compiler knows).
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+typedef u32x2 u32x2_any __attribute__((aligned(1)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
 __device__ __forceinline__ u32x4 gload4_any(const void *p) {
     return *gptr(reinterpret_cast<const u32x4_any *>(p));
 }

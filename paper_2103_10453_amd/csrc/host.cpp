@@ -36,13 +36,24 @@ int next_pow2(int x) {
     return p;
 }
 
-// Bits needed for colours 0..n.
-// Distance tiles (64 x 64, I <= J) that lie within P_t (rows 0..p-1).
-long old_tiles(int p) {
-    const long j0 = p / kDistTile;
-    return j0 * (j0 + 1) / 2;
+// Rows of a distance unit: short ones give the most waves, tall ones read a column's
+// planes half as often and write its mirror in longer pieces.  Short | tall, us:
+// n = 50: 27 | 36 for 128 rows, 34 | 52 for 1024, 97 | 111 for 4096, 283 | 282 for
+// 8192, 3722 | 3654 for 32768; n = 10: 24 | 25 for 4096, 42 | 44 for 8192, 186 |
+// 148 for 16384.  (32 rows: 55, 95, 138, 314 and 3643; n = 10: 27, 46, 145.)
+int unit_rows(int m) { return m <= 8192 ? kDistShort : kDistTall; }
+
+// Distance units of the first `cols` of m columns, whole blocks.
+long units_below(int cols, int m) { return dist_units(cols / kDistCols, unit_rows(m)); }
+long all_units(int cols, int m) { return units_below(cols + kDistCols - 1, m); }
+
+// Distance units among P_t (rows 0..p-1 of 2p) that run beside the searches:
+// the whole column blocks, or, of the first alone, what P_t has of it.
+long old_units(int p) {
+    return p < 64 ? 0 : p < kDistCols ? all_units(p, 2 * p) : units_below(p, 2 * p);
 }
 
+// Bits needed for colours 0..n.
 int colour_bits(int n) {
     int b = 0;
     while ((1 << b) <= n) ++b;
@@ -490,15 +501,15 @@ void build_pipeline_args(plse_instance *h, int p, uint64_t seed) {
     // distances among P_t (rows 0..p-1) need nothing from this generation's
     // searches, so they are packed and computed beside them; the rest after
     const int B = colour_bits(h->n);
-    // (with no tile within P_t, p < 64, the rest packs all 2p rows)
-    const bool split = old_tiles(p) > 0;
-    A.pack_t = PackArgs{ctl, S_all, at<uint32_t>(h, L.planes), p, h->nv, st, W, B, 0};
-    A.pack = split ? PackArgs{ctl, S_all, at<uint32_t>(h, L.planes), p, h->nv, st, W, B, p}
-                   : PackArgs{ctl, S_all, at<uint32_t>(h, L.planes), m, h->nv, st, W, B, 0};
-    const int nt1 = (m + kDistTile - 1) / kDistTile;
-    A.dist_t = DistArgs{ctl, at<uint32_t>(h, L.planes), at<int16_t>(h, L.D), m, W, m, nt1, 0};
-    A.dist = DistArgs{ctl, at<uint32_t>(h, L.planes), at<int16_t>(h, L.D), m, W, m, nt1,
-                      (int32_t)old_tiles(p)};
+    // (with none among P_t, p < 64, the rest packs all 2p rows)
+    const bool split = old_units(p) > 0;
+    uint32_t *planes = at<uint32_t>(h, L.planes);
+    A.pack_t = PackArgs{ctl, S_all, planes, p, h->nv, st, W, B, 0, m};
+    A.pack = split ? PackArgs{ctl, S_all, planes, p, h->nv, st, W, B, p, m}
+                   : PackArgs{ctl, S_all, planes, m, h->nv, st, W, B, 0, m};
+    A.dist_t = DistArgs{ctl, planes, at<int16_t>(h, L.D), p, W, m, m, 0, (int32_t)old_units(p)};
+    A.dist = DistArgs{ctl, planes, at<int16_t>(h, L.D), m, W, m, m, (int32_t)units_below(p, m),
+                      (int32_t)all_units(m, m)};
     A.close = CloseArgs{ctl, at<int16_t>(h, L.D), at<int32_t>(h, L.deg), at<uint16_t>(h, L.adj),
                         m, m, h->nv, h->P.spacing};
     A.select = make_select(h, p, 0, seed, ctl, f_all, at<int16_t>(h, L.D), m,
@@ -666,9 +677,9 @@ int enqueue_local_search(Session &S, hipStream_t s) {
     return PLSE_OK;
 }
 
-// Bit planes of one half of P^all and the distance tiles of one tile range.
+// Bit planes of one half of P^all and the distances of one range of units.
 int enqueue_pack_dist(Session &S, PackArgs ArgBlock::*pk, DistArgs ArgBlock::*dt, int rows,
-                      long tiles, hipStream_t s) {
+                      long units, hipStream_t s) {
     size_t pack_threads = 0;
     for (plse_instance *h : S.hs)
         pack_threads = std::max(pack_threads, (size_t)rows * ((h->nv + 31) / 32));
@@ -681,7 +692,7 @@ int enqueue_pack_dist(Session &S, PackArgs ArgBlock::*pk, DistArgs ArgBlock::*dt
             if (colour_bits(h->n) == B) g.push_back(h);
         if (g.empty()) continue;
         RC_TRY(launch_over(g, dt, [&](const ArgList &L, int c) {
-            return launch_dist(L, c, tiles, B, s);
+            return launch_dist(L, c, units, B, unit_rows(2 * S.p), s);
         }));
     }
     return PLSE_OK;
@@ -689,7 +700,7 @@ int enqueue_pack_dist(Session &S, PackArgs ArgBlock::*pk, DistArgs ArgBlock::*dt
 
 // Distances among P_t, beside the generation's searches.
 int enqueue_old_dist(Session &S, hipStream_t s) {
-    return enqueue_pack_dist(S, &ArgBlock::pack_t, &ArgBlock::dist_t, S.p, old_tiles(S.p), s);
+    return enqueue_pack_dist(S, &ArgBlock::pack_t, &ArgBlock::dist_t, S.p, old_units(S.p), s);
 }
 
 // The generation's stages after the searches.  `mark` (may be null) records
@@ -700,9 +711,8 @@ int enqueue_rest(Session &S, hipStream_t s, hipEvent_t *mark = nullptr) {
     RC_TRY(launch_over(S.hs, &ArgBlock::best,
                        [&](const ArgList &L, int c) { return launch_best(L, c, s); }));
     if (mark) HIP_TRY(hipEventRecord(mark[0], s));
-    const long nt1 = (m + kDistTile - 1) / kDistTile;
-    RC_TRY(enqueue_pack_dist(S, &ArgBlock::pack, &ArgBlock::dist, old_tiles(p) > 0 ? p : m,
-                             nt1 * (nt1 + 1) / 2 - old_tiles(p), s));
+    RC_TRY(enqueue_pack_dist(S, &ArgBlock::pack, &ArgBlock::dist, old_units(p) > 0 ? p : m,
+                             all_units(m, m) - units_below(p, m), s));
     if (mark) HIP_TRY(hipEventRecord(mark[1], s));
     RC_TRY(launch_over(S.hs, &ArgBlock::close,
                        [&](const ArgList &L, int c) { return launch_close(L, c, m, s); }));
@@ -843,7 +853,7 @@ int session_begin(Session &S, const uint64_t *seeds, hipStream_t s) {
     }
     RC_TRY(capture([&](hipStream_t cs) { return enqueue_local_search(S, cs); }, &S.ls));
     RC_TRY(capture([&](hipStream_t cs) { return enqueue_rest(S, cs); }, &S.rest));
-    if (old_tiles(S.p) > 0) {
+    if (old_units(S.p) > 0) {
         RC_TRY(capture([&](hipStream_t cs) { return enqueue_old_dist(S, cs); }, &S.dold));
         HIP_TRY(hipStreamCreateWithFlags(&S.dstream, hipStreamNonBlocking));
         HIP_TRY(hipEventCreateWithFlags(&S.dfork, hipEventDisableTiming));
@@ -873,7 +883,7 @@ int session_step(Session &S, int generations, hipStream_t s) {
             const size_t k = 3 * (size_t)(S.steps + g);
             hipEvent_t *m = &S.sev[(kStages + 1) * (size_t)(S.steps + g)];
             HIP_TRY(hipEventRecord(m[0], s));
-            if (old_tiles(S.p) > 0) RC_TRY(enqueue_old_dist(S, s));
+            if (old_units(S.p) > 0) RC_TRY(enqueue_old_dist(S, s));
             HIP_TRY(hipEventRecord(m[1], s));
             HIP_TRY(hipEventRecord(S.ev[k], s));
             RC_TRY(enqueue_local_search(S, s));
@@ -1048,7 +1058,7 @@ int solve_direct(plse_instance *h, int p, int G, uint64_t seed, hipStream_t s,
     shape_session(S);
     if (S.groups.size() != 1) return PLSE_E_ARG;
     for (int g = 0; g < G; ++g) {
-        if (old_tiles(p) > 0) RC_TRY(enqueue_old_dist(S, s));
+        if (old_units(p) > 0) RC_TRY(enqueue_old_dist(S, s));
         RC_TRY(enqueue_local_search(S, s));
         RC_TRY(enqueue_rest(S, s));
     }
@@ -1889,12 +1899,13 @@ int plse_stage_distances(plse_handle h, int32_t m, void *stream, const uint8_t *
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     RC_TRY(stage_prepare(h, std::max(2, (m + 1) / 2), s, Tables::none));
     const int W = (h->nv + 31) / 32, B = colour_bits(h->n);
-    h->args.pack = PackArgs{nullptr, S, at<uint32_t>(h, h->L.planes), m, h->nv, h->stride, W, B, 0};
-    const int nt1 = (m + kDistTile - 1) / kDistTile;
-    h->args.dist = DistArgs{nullptr, at<uint32_t>(h, h->L.planes), D, m, W, m, nt1, 0};
+    const int pitch = 2 * std::max(2, (m + 1) / 2);  // rows that the workspace has planes for
+    uint32_t *planes = at<uint32_t>(h, h->L.planes);
+    h->args.pack = PackArgs{nullptr, S, planes, m, h->nv, h->stride, W, B, 0, pitch};
+    h->args.dist = DistArgs{nullptr, planes, D, m, W, m, pitch, 0, (int32_t)all_units(m, m)};
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_pack(single(h, &ArgBlock::pack), 1, (size_t)m * W, s));
-    HIP_TRY(launch_dist(single(h, &ArgBlock::dist), 1, (long)nt1 * (nt1 + 1) / 2, B, s));
+    HIP_TRY(launch_dist(single(h, &ArgBlock::dist), 1, all_units(m, m), B, unit_rows(m), s));
     return PLSE_OK;
 }
 

@@ -114,159 +114,172 @@ __global__ __launch_bounds__(1024) void best_kernel(const ArgList L) {
 
 // ---------------------------------------------------------------------------
 // Hamming distances (Eq. 8), bit-sliced.  pack: colour bit b of vertices
-// 32w..32w+31 of row x -> planes[(x*W + w)*B + b].  A pair differs at v iff
+// 32w..32w+31 of row x -> planes[(w*pitch + x)*B + b].  A pair differs at v iff
 // some plane differs, so D = sum_w popcount(OR_b (a_b XOR c_b)).
 // ---------------------------------------------------------------------------
 
+// One thread per row and word: 32 colours as eight u32 words; the bits b of a
+// word's four bytes are brought together by a multiplication.  32768 rows of
+// n = 50: 45 us (byte by byte: 95), of which 41 MB in and 31 MB out take 14.
 __global__ __launch_bounds__(256) void pack_kernel(const ArgList L) {
     const PackArgs a = arg_of<PackArgs>(L);
     if (a.ctl && a.ctl->stop) return;
     const size_t t = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= (size_t)a.m * a.W) return;
     const int x = a.row0 + (int)(t / a.W), w = (int)(t % a.W);
-    const uint8_t *row = a.S + (size_t)x * a.stride;
-    uint32_t pl[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    const int v0 = w * 32;
-    const int vend = min(a.nv, v0 + 32);
-    for (int v = v0; v < vend; ++v) {
-        const uint32_t s = row[v];
+    const uint8_t *row = a.S + (size_t)x * a.stride + 32 * w;
+    const u32x4 lo = gload4_any(row);
+    u32x4 hi = {0u, 0u, 0u, 0u};
+    if (32 * w + 16 < a.stride) hi = gload4_any(row + 16);
+    const uint32_t s[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    const int left = a.nv - 32 * w;  // vertices in the word
+    const uint32_t valid = left >= 32 ? 0xFFFFFFFFu : (1u << left) - 1u;
+    uint32_t *dst = a.planes + ((size_t)w * a.pitch + x) * a.B;
+    for (int b = 0; b < a.B; ++b) {
+        uint32_t pl = 0u;
 #pragma unroll
-        for (int b = 0; b < 8; ++b) pl[b] |= ((s >> b) & 1u) << (v - v0);
+        for (int q = 0; q < 8; ++q)
+            pl |= ((((s[q] >> b) & 0x01010101u) * 0x01020408u) >> 24) << (4 * q);
+        gptr(dst)[b] = pl & valid;
     }
-    uint32_t *dst = a.planes + ((size_t)x * a.W + w) * a.B;
-    for (int b = 0; b < a.B; ++b) dst[b] = pl[b];
 }
 
-constexpr int kTile = kDistTile;  // rows and columns per distance tile
-constexpr int kCW = 8;      // words of 32 vertices staged per step
-
-
-// One 64x64 tile (I <= J) per 256-thread workgroup; each thread owns a 4x4
-// block of pairs (rows ty+16i, columns tx+16j).  The output tile reuses the
-// operand LDS, so more workgroups fit per CU.  Both D[I][J] and its mirror
-// are written through that LDS tile so that stores are row-contiguous.
+// The planes of a lane's two adjacent columns, as they are loaded.
 template <int B>
+struct Columns {
+    u32x4 four[B / 2 > 0 ? B / 2 : 1];
+    u32x2 two;
+    __device__ uint32_t at(int i) const { return i < B / 2 * 4 ? four[i / 4][i % 4] : two[i % 2]; }
+};
+
+// One wave per unit of R rows x 128 columns, two adjacent columns a lane.  The
+// rows' planes are wave-uniform: scalar loads, and the scalar operand of the
+// XOR-OR; the columns' planes and the sums are in registers.  So nothing passes
+// through LDS and nearly all issued instructions are the B + 1 of a pair and
+// word.  The next group of rows and the next word's columns are loaded ahead
+// (without: 5.1 ms in the case below, the waves waiting for scalar loads).  Units
+// of a column block j cover the rows up to its last column, so every pair is in
+// one; D[row][column] and its mirror are both written.
+//
+// Bound by the VALU: 32768 rows of n = 50, half prefilled (40 words of 6
+// planes), take 3.6 ms: the 7 operations of every pair and word run at 41 T/s, one
+// instruction a SIMD every four cycles.  Tiles of 64 x 64 staged through LDS,
+// 4 x 4 pairs a thread, took 5.06 ms (1024 rows: 70 us more).
+template <int B, int R>
 __global__ __launch_bounds__(256) void dist_kernel(const ArgList L) {
     const DistArgs a = arg_of<DistArgs>(L);
     if (a.ctl && a.ctl->stop) return;
-    // even pitch with 64-bit reads: 16 rows at a pitch of kCW*B + 2 words
-    // (50 for B = 6) start in distinct even banks, so the bank pairs of a
-    // 64-bit read never collide; plane pairs stay 8-byte aligned
-    constexpr int PITCH = (B % 2 == 0) ? kCW * B + 2 : kCW * B + 1;
-    constexpr int OPW = 2 * kTile * PITCH;             // operand words
-    constexpr int DTW = kTile * (kTile + 2) / 2;       // output tile words
-    __shared__ uint32_t AB[OPW > DTW ? OPW : DTW];
-    uint32_t *As = AB, *Bs = AB + kTile * PITCH;
-    int16_t(*Dt)[kTile + 2] = reinterpret_cast<int16_t(*)[kTile + 2]>(AB);
-    // triangular tile index -> (I, J), I <= J
-    const long t = (long)blockIdx.x + a.tile0;
-    long J = (long)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
-    while ((J + 1) * (J + 2) / 2 <= t) ++J;
-    while (J * (J + 1) / 2 > t) --J;
-    const long I = t - J * (J + 1) / 2;
-    const int r0 = (int)I * kTile, c0 = (int)J * kTile;
-    const int tid = (int)threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    uint32_t acc[4][4];
+    const int t = readfirst((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) + a.unit0;
+    if (t >= a.unit1) return;
+    // unit -> column block j, and the row block within it
+    constexpr int kHalf = kDistCols / R / 2;  // kHalf j (j + 1) units before block j
+    int j = (int)((sqrtf(4.0f / kHalf * (float)t + 1.0f) - 1.0f) * 0.5f);
+    while (kHalf * (j + 1) * (j + 2) <= t) ++j;
+    while (kHalf * j * (j + 1) > t) --j;
+    j = readfirst(j);
+    const int r0 = R * (t - kHalf * j * (j + 1)), c = kDistCols * j + 2 * lane_id();
+    if (r0 >= a.m) return;
+    // (the pitch is even, so either both of a lane's columns lie within or none is used)
+    const uint32_t oc = (uint32_t)min(c, a.pitch - 2) * B;
+    constexpr int kG = 4;  // rows per group of scalar loads
+    constexpr int kGroups = R / kG;
+    const uint32_t wstep = (uint32_t)a.pitch * B;
+    uint32_t acc[R][2];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < R; ++i) acc[i][0] = acc[i][1] = 0u;
+    Columns<B> col[2];
+    uint32_t row[2][kG * B];
+    auto columns = [&](Columns<B> &x, const uint32_t *planes) {
+        const uint32_t *base = planes + oc;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0u;
-
-    for (int w0 = 0; w0 < a.W; w0 += kCW) {
-        const int nw = min(kCW, a.W - w0);
-        // stage kTile rows x nw words x B planes for both sides
-        if constexpr (B % 2 == 0) {
-            // plane pairs: 8-byte global loads and LDS stores (rows of B
-            // words per vertex word keep pairs 8-byte aligned on both sides)
-            constexpr int HP = kCW * B / 2;  // pairs per staged row
-            for (int q = tid; q < kTile * HP; q += 256) {
-                const int row = q / HP, rem = 2 * (q % HP);
-                const int wc = rem / B;
-                u32x2 va{0u, 0u}, vb{0u, 0u};
-                if (wc < nw) {
-                    const int ra = r0 + row, rb = c0 + row;
-                    if (ra < a.m)
-                        va = *gptr(reinterpret_cast<const u32x2 *>(
-                            a.planes + ((size_t)ra * a.W + w0) * B + rem));
-                    if (rb < a.m)
-                        vb = *gptr(reinterpret_cast<const u32x2 *>(
-                            a.planes + ((size_t)rb * a.W + w0) * B + rem));
+        for (int q = 0; q < B / 2; ++q) x.four[q] = gload4_any(base + 4 * q);
+        if constexpr (B & 1)
+            x.two = *gptr(reinterpret_cast<const u32x2_any *>(base + 2 * B - 2));
+    };
+    auto rows = [&](uint32_t (&x)[kG * B], const uint32_t *planes, int g) {
+        // (the last rows of the planes again, past the end)
+        const auto *pr = cptr(planes + (uint32_t)min(r0 + kG * g, a.pitch - kG) * B);
+#pragma unroll
+        for (int i = 0; i < kG * B; ++i) x[i] = pr[i];
+    };
+    // one word; the next group of rows and the next word's columns are on their way
+    const uint32_t *at = a.planes;
+    auto word = [&](int w, const Columns<B> &now, Columns<B> &next) {
+        const uint32_t *const here = at;
+        if (w + 1 < a.W) at += wstep;
+        columns(next, at);
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            uint32_t(&cur)[kG * B] = row[g & 1];
+            // scalar loads return in any order: wait for these before the next are issued
+            asm volatile("" ::"s"(cur[0]), "s"(cur[kG * B - 1]));
+            if (g + 1 < kGroups)
+                rows(row[(g + 1) & 1], here, g + 1);
+            else
+                rows(row[(g + 1) & 1], at, 0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < kG; ++i) {
+                uint32_t x = cur[i * B] ^ now.at(0), y = cur[i * B] ^ now.at(B);
+#pragma unroll
+                for (int b = 1; b < B; ++b) {
+                    // v_bitop3 with table 0xBE = (s0 ^ s1) | s2
+                    x = __builtin_amdgcn_bitop3_b32(cur[i * B + b], now.at(b), x, 0xBE);
+                    y = __builtin_amdgcn_bitop3_b32(cur[i * B + b], now.at(B + b), y, 0xBE);
                 }
-                *reinterpret_cast<u32x2 *>(As + row * PITCH + rem) = va;
-                *reinterpret_cast<u32x2 *>(Bs + row * PITCH + rem) = vb;
+                acc[kG * g + i][0] += (uint32_t)__popc(x);
+                acc[kG * g + i][1] += (uint32_t)__popc(y);
+                // (v_bcnt adds to its sum; regrouped, two words' counts would need a
+                // third addition)
+                asm volatile("" : "+v"(acc[kG * g + i][0]), "+v"(acc[kG * g + i][1]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    if (a.W > 0) rows(row[0], at, 0);
+    if (a.W & 1) {
+        columns(col[1], at);
+        word(0, col[1], col[0]);
+    } else if (a.W > 0) {
+        columns(col[0], at);
+    }
+    for (int w = a.W & 1; w < a.W; w += 2) {
+        word(w, col[0], col[1]);
+        word(w + 1, col[1], col[0]);
+    }
+    // rows: two columns a lane, 256 bytes a row and wave
+    const bool two = c + 1 < a.m, one = c < a.m;
+    const bool whole = r0 + R <= a.m;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        const int g = i / kG, r = min(r0 + kG * g, a.pitch - kG) + i % kG;
+        if (r >= a.m) continue;
+        int16_t *d = a.D + (size_t)r * a.ld + c;
+        if (two)
+            *gptr(reinterpret_cast<u32_any *>(d)) = acc[i][0] | (acc[i][1] << 16);
+        else if (one)
+            *gptr(d) = (int16_t)acc[i][0];
+    }
+    // mirror: the R rows of a column are adjacent in its row
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+        if (z == 0 ? !one : !two) continue;
+        int16_t *d = a.D + (size_t)(c + z) * a.ld + r0;
+        if (whole) {
+#pragma unroll
+            for (int q = 0; q < R / 8; ++q) {
+                u32x4 v;
+#pragma unroll
+                for (int h = 0; h < 4; ++h)
+                    v[h] = acc[8 * q + 2 * h][z] | (acc[8 * q + 2 * h + 1][z] << 16);
+                *gptr(reinterpret_cast<u32x4_any *>(d) + q) = v;
             }
         } else {
-            for (int q = tid; q < kTile * kCW * B; q += 256) {
-                const int row = q / (kCW * B), rem = q % (kCW * B);
-                const int wc = rem / B;
-                uint32_t va = 0u, vb = 0u;
-                if (wc < nw) {
-                    const int ra = r0 + row, rb = c0 + row;
-                    if (ra < a.m) va = *gptr(a.planes + ((size_t)ra * a.W + w0) * B + rem);
-                    if (rb < a.m) vb = *gptr(a.planes + ((size_t)rb * a.W + w0) * B + rem);
-                }
-                As[row * PITCH + rem] = va;
-                Bs[row * PITCH + rem] = vb;
+#pragma unroll
+            for (int i = 0; i < R; ++i) {
+                const int g = i / kG, r = min(r0 + kG * g, a.pitch - kG) + i % kG;
+                if (r < a.m) *gptr(a.D + (size_t)(c + z) * a.ld + r) = (int16_t)acc[i][z];
             }
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int wc = 0; wc < nw; ++wc) {
-            uint32_t ra[4][B], rb[4][B];
-            if constexpr (B % 2 == 0) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int b = 0; b < B; b += 2) {
-                        const u32x2 x = *reinterpret_cast<const u32x2 *>(
-                            As + (ty + 16 * i) * PITCH + wc * B + b);
-                        const u32x2 y = *reinterpret_cast<const u32x2 *>(
-                            Bs + (tx + 16 * i) * PITCH + wc * B + b);
-                        ra[i][b] = x.x;
-                        ra[i][b + 1] = x.y;
-                        rb[i][b] = y.x;
-                        rb[i][b + 1] = y.y;
-                    }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int b = 0; b < B; ++b) {
-                        ra[i][b] = As[(ty + 16 * i) * PITCH + wc * B + b];
-                        rb[i][b] = Bs[(tx + 16 * i) * PITCH + wc * B + b];
-                    }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    // OR over planes of the XOR: one 3-input op per plane
-                    // (v_bitop3 with table 0xBE = (s0 ^ s1) | s2)
-                    uint32_t x = ra[i][0] ^ rb[j][0];
-#pragma unroll
-                    for (int b = 1; b < B; ++b)
-                        x = __builtin_amdgcn_bitop3_b32(ra[i][b], rb[j][b], x, 0xBE);
-                    acc[i][j] += (uint32_t)__popc(x);
-                }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) Dt[ty + 16 * i][tx + 16 * j] = (int16_t)acc[i][j];
-    __syncthreads();
-    // rows of the tile: D[r0 + row][c0 .. c0+63]
-    for (int q = tid; q < kTile * kTile; q += 256) {
-        const int row = q >> 6, col = q & 63;
-        const int gr = r0 + row, gc = c0 + col;
-        if (gr < a.m && gc < a.m) *gptr(a.D + (size_t)gr * a.ld + gc) = Dt[row][col];
-    }
-    if (I != J) {
-        for (int q = tid; q < kTile * kTile; q += 256) {
-            const int row = q >> 6, col = q & 63;  // mirror: D[c0 + row][r0 + col]
-            const int gr = c0 + row, gc = r0 + col;
-            if (gr < a.m && gc < a.m) *gptr(a.D + (size_t)gr * a.ld + gc) = Dt[col][row];
         }
     }
 }
@@ -895,23 +908,25 @@ hipError_t launch_pack(const ArgList &L, int count, size_t max_threads, hipStrea
     return hipGetLastError();
 }
 
-hipError_t launch_dist(const ArgList &L, int count, long tiles, int B, hipStream_t stream) {
-    if (tiles <= 0) return hipSuccess;
-    const dim3 grid((unsigned)tiles, count);
+hipError_t launch_dist(const ArgList &L, int count, long units, int B, int rows,
+                       hipStream_t stream) {
+    if (units <= 0) return hipSuccess;
+    const dim3 grid((unsigned)((units + 3) / 4), count);
+    auto go = [&](auto kernel_short, auto kernel_tall) {
+        void (*k)(const ArgList) = rows == kDistShort ? kernel_short : kernel_tall;
+        hipLaunchKernelGGL(k, grid, 256, 0, stream, L);
+        return hipGetLastError();
+    };
     switch (B) {
-#define PLSE_DIST_CASE(b) \
-    case b: hipLaunchKernelGGL(dist_kernel<b>, grid, dim3(256), 0, stream, L); break;
-        PLSE_DIST_CASE(1)
-        PLSE_DIST_CASE(2)
-        PLSE_DIST_CASE(3)
-        PLSE_DIST_CASE(4)
-        PLSE_DIST_CASE(5)
-        PLSE_DIST_CASE(6)
-        PLSE_DIST_CASE(7)
-#undef PLSE_DIST_CASE
+        case 1: return go(dist_kernel<1, kDistShort>, dist_kernel<1, kDistTall>);
+        case 2: return go(dist_kernel<2, kDistShort>, dist_kernel<2, kDistTall>);
+        case 3: return go(dist_kernel<3, kDistShort>, dist_kernel<3, kDistTall>);
+        case 4: return go(dist_kernel<4, kDistShort>, dist_kernel<4, kDistTall>);
+        case 5: return go(dist_kernel<5, kDistShort>, dist_kernel<5, kDistTall>);
+        case 6: return go(dist_kernel<6, kDistShort>, dist_kernel<6, kDistTall>);
+        case 7: return go(dist_kernel<7, kDistShort>, dist_kernel<7, kDistTall>);
         default: return hipErrorInvalidValue;
     }
-    return hipGetLastError();
 }
 
 hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream) {

@@ -266,12 +266,6 @@ struct Best {
     uint32_t hi, id, pay;
 };
 
-// Instance tables at wave-uniform addresses: scalar loads.
-template <typename T>
-__device__ __forceinline__ const __attribute__((address_space(4))) T *cptr(const T *p) {
-    return (const __attribute__((address_space(4))) T *)p;
-}
-
 // v * u of 24-bit factors, u uniform (a full 32-bit product takes four times
 // as long).
 __device__ __forceinline__ uint32_t mul24(uint32_t v, uint32_t u) {

@@ -89,20 +89,23 @@ struct BestArgs {
 struct PackArgs {
     const Ctl *ctl;
     const uint8_t *S;        // [rows][stride]
-    uint32_t *planes;        // [rows][W][B]
+    uint32_t *planes;        // [W][pitch][B]
     int32_t m, nv, stride, W, B;  // m: rows packed, from row row0
-    int32_t row0;
+    int32_t row0, pitch;
 };
 
 struct DistArgs {
     const Ctl *ctl;
-    const uint32_t *planes;  // [m][W][B]
+    const uint32_t *planes;  // [W][pitch][B], pitch >= 4 and even
     int16_t *D;              // [m][ld]
-    int32_t m, W, ld, ntiles;  // ntiles: per side (ceil(m / kDistTile))
-    int32_t tile0;             // first triangular tile index of the launch
+    int32_t m, W, ld, pitch;
+    int32_t unit0, unit1;    // the launch's units of 8 or 16 rows x kDistCols columns
 };
 
-constexpr int kDistTile = 64;  // rows and columns per distance tile
+constexpr int kDistCols = 128;  // columns of a distance unit
+constexpr int kDistShort = 8, kDistTall = 16;  // rows of a unit
+// Units of the column blocks before j (block j: rows up to its last column).
+constexpr long dist_units(long j, int rows) { return kDistCols / rows / 2 * j * (j + 1); }
 
 struct CloseArgs {
     const Ctl *ctl;
@@ -203,8 +206,9 @@ size_t init_lds_bytes(const DevInstance &I);
 hipError_t init_set_lds_limit(int bytes);
 hipError_t launch_best(const ArgList &L, int count, hipStream_t stream);
 hipError_t launch_pack(const ArgList &L, int count, size_t max_threads, hipStream_t stream);
-// tiles: triangular tiles (I <= J) of the launch, from the arg block's tile0
-hipError_t launch_dist(const ArgList &L, int count, long tiles, int B, hipStream_t stream);
+// units: the most of one instance's unit1 - unit0
+hipError_t launch_dist(const ArgList &L, int count, long units, int B, int rows,
+                       hipStream_t stream);
 hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream);
 hipError_t launch_select(const ArgList &L, int count, size_t lds, int pow2, bool keys_in_lds,
                          hipStream_t stream);

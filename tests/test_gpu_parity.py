@@ -231,6 +231,40 @@ def test_distances_parity(torch_cuda, oracle_mod, name, m):
     np.testing.assert_array_equal(_np(D).astype(np.int32), Do)
 
 
+@pytest.mark.parametrize("n,m", [(3, 2), (7, 3), (12, 5), (20, 31), (40, 33), (70, 63), (12, 127),
+                                 (40, 129), (70, 257), (40, 2046), (20, 2048), (12, 2081),
+                                 (3, 8192), (12, 8193), (40, 8207), (20, 8337)])
+def test_distances_units(torch_cuda, oracle_mod, n, m):
+    """Rows and columns at the edges of a distance unit, short units and tall
+    (more than 8192 rows), every number of colour planes, solutions and distances at
+    odd addresses; nothing is written outside the m rows."""
+    import torch
+    _say(f"distance units n={n} m={m}")
+    rng = np.random.default_rng(1000 * n + m)
+    i, j = np.indices((n, n))
+    g = ((i + j) % n + 1) * (rng.random((n, n)) < (0.8 if n > 30 else 0.3))
+    s = P.Solver(g)
+    I = oracle_mod.Instance(g)
+    S = rng.integers(0, 256, size=(m, s.stride), dtype=np.uint8)  # (past nv: anything)
+    S[:, :I.nv] = rng.integers(0, I.n + 1, size=(m, I.nv))
+    S[rng.integers(0, m, size=m // 4), :I.nv] = S[0, :I.nv]
+    for byte, word in ((0, 0), (3, 1)):
+        Sd = torch.zeros(S.size + 16, dtype=torch.uint8, device="cuda")
+        Sd[byte:byte + S.size] = torch.from_numpy(S.ravel()).cuda()
+        Dd = torch.full((m * m + 16,), -7, dtype=torch.int16, device="cuda")
+        s.ensure_workspace(max(2, (m + 1) // 2))
+        P.plse_stage_distances(s.h, m, Sd[byte:], Dd[word:])
+        torch.cuda.synchronize()
+        D = _np(Dd)
+        assert (D[:word] == -7).all() and (D[word + m * m:] == -7).all()
+        D = D[word:word + m * m].reshape(m, m)
+        rows = np.arange(m) if m < 3000 else np.concatenate(
+            [[0, 1, 15, 16, 127, 128], rng.integers(0, m, size=100), np.arange(8180, m)])
+        np.testing.assert_array_equal(D[rows].astype(np.int32),
+                                      oracle_mod.distances(S[rows, :I.nv], S[:, :I.nv]))
+        np.testing.assert_array_equal(D, D.T)
+
+
 @pytest.mark.parametrize("p,gen_no,seed,global_sort", [(2, 1, 1, 0), (64, 3, 5, 0),
                                                        (100, 7, 11, 0), (300, 2, 13, 0),
                                                        (1024, 4, 17, 0), (2100, 5, 19, 1),
