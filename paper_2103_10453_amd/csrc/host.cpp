@@ -65,7 +65,7 @@ struct Layout {
     size_t vrc, vrec, cand, vinfo, nbr, rcl, rclo;
     size_t args, ctl, stats, Sstar;
     size_t S_all, S_off, S_tmp, f_all, f_tmp, uid, uid_tmp, hist, hist_tmp, hc, hc_tmp, cnt;
-    size_t tabu, planes, D, deg, adj, keys, acc, pos, hkeys, hvals, partner, dpart;
+    size_t tabu, planes, D, deg, adj, keys, order, acc, pos, hkeys, hvals, partner, dpart;
     size_t queue;  // work queue of a persistent batched search launch led by this instance
     size_t total;
     int pow2_sel, hsize;
@@ -339,6 +339,7 @@ Layout plan(const plse_instance *h, int p) {
     L.adj = take(2 * m * kAdj);
     L.pow2_sel = next_pow2(std::max<int>(4, (int)m));
     L.keys = take(8 * (size_t)L.pow2_sel);
+    L.order = take(2 * m);
     L.acc = take(4 * (size_t)p);
     L.pos = take(4 * m);
     L.hsize = next_pow2(std::max<int>(4, (int)m));
@@ -456,6 +457,7 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
     a.deg = at<int32_t>(h, L.deg);
     a.adj = at<uint16_t>(h, L.adj);
     a.keys_g = at<uint64_t>(h, L.keys);
+    a.order = at<uint16_t>(h, L.order);
     a.acc = acc;
     a.pos = at<int32_t>(h, L.pos);
     a.p = p;
@@ -463,8 +465,8 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
     a.ld = ld;
     a.nv = h->nv;
     a.pow2 = L.pow2_sel;
-    // keys in LDS when they fit; the global-memory sort needs at least two
-    // 4096-key tiles
+    // keys in LDS when they fit; the sort in global memory takes whole tiles
+    // (8192 keys at least)
     const bool fits = select_lds_bytes(2 * p, L.pow2_sel, true) <= (size_t)max_lds_per_block();
     a.keys_in_lds = (fits && !(h->sel_global && L.pow2_sel >= 8192)) || L.pow2_sel < 8192 ? 1 : 0;
     a.gen_fixed = gen_fixed;
@@ -720,7 +722,7 @@ int enqueue_rest(Session &S, hipStream_t s, hipEvent_t *mark = nullptr) {
     const int pow2 = S.hs[0]->L.pow2_sel;
     const bool keys_lds = S.hs[0]->args.select.keys_in_lds != 0;
     RC_TRY(launch_over(S.hs, &ArgBlock::select, [&](const ArgList &L, int c) {
-        return launch_select(L, c, sl, pow2, keys_lds, s);
+        return launch_select(L, c, sl, m, pow2, keys_lds, s);
     }));
     RC_TRY(launch_over(S.hs, &ArgBlock::gather,
                        [&](const ArgList &L, int c) { return launch_gather(L, c, p, s); }));
@@ -1922,7 +1924,7 @@ int plse_stage_select(plse_handle h, int32_t p, int32_t gen, uint64_t seed, void
     h->args.select = make_select(h, p, gen, seed, nullptr, f_all, D_all, m, accepted);
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_close(single(h, &ArgBlock::close), 1, m, s));
-    HIP_TRY(launch_select(single(h, &ArgBlock::select), 1, select_lds(h, p), h->L.pow2_sel,
+    HIP_TRY(launch_select(single(h, &ArgBlock::select), 1, select_lds(h, p), 2 * p, h->L.pow2_sel,
                           h->args.select.keys_in_lds != 0, s));
     return PLSE_OK;
 }

@@ -353,7 +353,7 @@ __global__ __launch_bounds__(256) void close_kernel(const ArgList L) {
 
 
 // Selection keys of P^all: f << 48 | SELECT draw << 16 | index (the order of
-// Alg. 4: e, then a random key, then the index), ~0 beyond m.
+// Alg. 4: e, then a random key, then the index), ~0 beyond m: the four from 4q on.
 __device__ __forceinline__ void select_keys(const SelectArgs &a, uint32_t gen, int q,
                                             uint64_t *K) {
     const int x0 = q * 4;
@@ -362,7 +362,7 @@ __device__ __forceinline__ void select_keys(const SelectArgs &a, uint32_t gen, i
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
         const int x = x0 + t;
-        K[x] = (x < a.m) ? (((uint64_t)(uint32_t)a.f_all[x] << 48) |
+        K[t] = (x < a.m) ? (((uint64_t)(uint32_t)a.f_all[x] << 48) |
                             ((uint64_t)word_of(w, t) << 16) | (uint32_t)x)
                          : ~0ull;
     }
@@ -378,36 +378,31 @@ __device__ __forceinline__ bool select_gen(const SelectArgs &a, uint32_t *gen) {
     return true;
 }
 
-// Key sort for populations whose keys exceed LDS: a bitonic network over the
-// global key array, tile-local stages (partner distance < kSortTile) in LDS.
-constexpr int kSortTile = 4096;
-
-__global__ __launch_bounds__(256) void select_keys_kernel(const ArgList L) {
-    const SelectArgs a = arg_of<SelectArgs>(L);
-    uint32_t gen;
-    if (!select_gen(a, &gen)) return;
-    const int q = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (q < (a.pow2 >> 2)) select_keys(a, gen, q, a.keys_g);
-}
-
 // Pair i of a bitonic step with partner distance j: lower index.
 __device__ __forceinline__ int bitonic_lo(int i, int j) { return ((i & ~(j - 1)) << 1) | (i & (j - 1)); }
 
-__global__ __launch_bounds__(1024) void sort_tile_kernel(const ArgList L, int k_lo, int k_hi) {
+// Key sort for populations whose keys exceed LDS: tiles sorted in LDS, then each
+// key's place is the sum of its place in every tile (binary searches; the keys
+// differ).  Bound by latency: the 66 steps of a tile, then 24 dependent reads.
+// 32768 keys: 35 us; a bitonic network over the whole array, tile-local
+// steps in LDS, took 95 in ten launches.
+constexpr int kSortTile = 2048;
+
+__global__ __launch_bounds__(1024) void sort_tile_kernel(const ArgList L) {
     __shared__ uint64_t t[kSortTile];
     const SelectArgs a = arg_of<SelectArgs>(L);
     uint32_t gen;
     if (!select_gen(a, &gen)) return;
     const int base = (int)blockIdx.x * kSortTile;
-    for (int q = (int)threadIdx.x; q < kSortTile; q += (int)blockDim.x) t[q] = a.keys_g[base + q];
+    for (int q = (int)threadIdx.x; q < (kSortTile >> 2); q += (int)blockDim.x)
+        select_keys(a, gen, (base >> 2) + q, t + 4 * q);
     __syncthreads();
-    for (int k = k_lo; k <= k_hi; k <<= 1) {
-        for (int j = min(k >> 1, kSortTile >> 1); j > 0; j >>= 1) {
+    for (int k = 2; k <= kSortTile; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
             for (int i = (int)threadIdx.x; i < (kSortTile >> 1); i += (int)blockDim.x) {
                 const int lo = bitonic_lo(i, j), hi = lo + j;
-                const bool up = ((base + lo) & k) == 0;
                 const uint64_t x = t[lo], y = t[hi];
-                if ((x > y) == up) {
+                if ((x > y) == ((lo & k) == 0)) {
                     t[lo] = y;
                     t[hi] = x;
                 }
@@ -418,20 +413,33 @@ __global__ __launch_bounds__(1024) void sort_tile_kernel(const ArgList L, int k_
     for (int q = (int)threadIdx.x; q < kSortTile; q += (int)blockDim.x) a.keys_g[base + q] = t[q];
 }
 
-__global__ __launch_bounds__(256) void sort_global_kernel(const ArgList L, int k, int j) {
+__global__ __launch_bounds__(256) void sort_rank_kernel(const ArgList L, int tiles) {
     const SelectArgs a = arg_of<SelectArgs>(L);
     uint32_t gen;
     if (!select_gen(a, &gen)) return;
-    const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    if (i >= (a.pow2 >> 1)) return;
-    const int lo = bitonic_lo(i, j), hi = lo + j;
-    const bool up = (lo & k) == 0;
-    uint64_t *K = a.keys_g;
-    const uint64_t x = K[lo], y = K[hi];
-    if ((x > y) == up) {
-        K[lo] = y;
-        K[hi] = x;
+    const int q = (int)(blockIdx.x * blockDim.x + threadIdx.x);  // < tiles * kSortTile
+    const uint64_t key = *gptr(a.keys_g + q);
+    const int own = q / kSortTile;
+    int place = q % kSortTile;
+    constexpr int kAhead = 8;  // searches side by side
+    for (int t0 = 0; t0 < tiles; t0 += kAhead) {
+        int lo[kAhead];
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) lo[h] = 0;
+        auto tile = [&](int h) { return a.keys_g + (size_t)min(t0 + h, tiles - 1) * kSortTile; };
+        for (int step = kSortTile >> 1; step > 0; step >>= 1) {
+#pragma unroll
+            for (int h = 0; h < kAhead; ++h)
+                lo[h] += *gptr(tile(h) + lo[h] + step - 1) < key ? step : 0;
+        }
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) {
+            const int below = lo[h] + (*gptr(tile(h) + lo[h]) < key ? 1 : 0);
+            place += t0 + h < tiles && t0 + h != own ? below : 0;
+        }
     }
+    // (the fill of the last tile ranks past all keys)
+    if (place < a.m) *gptr(a.order + place) = (uint16_t)key;
 }
 
 // One workgroup: keys (f, SELECT draw, index) sorted (here by a bitonic network
@@ -465,7 +473,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
     const int nbw = (m + 31) / 32;
     const bool klds = a.keys_in_lds != 0;
     // keys (then the candidates in order, and each candidate's place in it);
-    // with the keys in global memory the places alone
+    // with the order in global memory the places alone
     uint64_t *K = reinterpret_cast<uint64_t *>(lds);
     uint16_t *rank = reinterpret_cast<uint16_t *>(lds);
     uint16_t *order = rank + P2;
@@ -475,7 +483,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
     uint32_t *gpre = accb + nbw;     // accepted before each group of 64 places
 
     if (klds)
-        for (int q = tid; q < (P2 >> 2); q += nthr) select_keys(a, gen, q, K);
+        for (int q = tid; q < (P2 >> 2); q += nthr) select_keys(a, gen, q, K + 4 * q);
     for (int q = tid; q < 2 * nbw; q += nthr) blocked[q] = 0u;
     for (int q = tid; q < m; q += nthr) *gptr(a.pos + q) = -1;
     if (tid < 32) s_wait[0][tid] = s_wait[1][tid] = 0u;
@@ -514,11 +522,11 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
         }
     } else {
         for (int r = tid; r < m; r += nthr)
-            rank[(uint32_t)*gptr(a.keys_g + r) & 0xFFFFu] = (uint16_t)r;
+            rank[*gptr(a.order + r)] = (uint16_t)r;
     }
     __syncthreads();
     auto order_at = [&](int r) -> int {
-        return klds ? (int)order[r] : (int)((uint32_t)*gptr(a.keys_g + r) & 0xFFFFu);
+        return klds ? (int)order[r] : (int)*gptr(a.order + r);
     };
     auto is_blocked = [&](int x) -> bool { return (blocked[x >> 5] >> (x & 31)) & 1u; };
 
@@ -934,22 +942,14 @@ hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream) 
     return hipGetLastError();
 }
 
-hipError_t launch_select(const ArgList &L, int count, size_t lds, int pow2, bool keys_in_lds,
-                         hipStream_t stream) {
+hipError_t launch_select(const ArgList &L, int count, size_t lds, int m, int pow2,
+                         bool keys_in_lds, hipStream_t stream) {
     if (!keys_in_lds) {
-        if (pow2 < kSortTile) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(select_keys_kernel, dim3((pow2 / 4 + 255) / 256, count), dim3(256), 0,
-                           stream, L);
-        const int tiles = pow2 / kSortTile;
-        hipLaunchKernelGGL(sort_tile_kernel, dim3(tiles, count), dim3(1024), 0, stream, L, 2,
-                           kSortTile);
-        for (int k = 2 * kSortTile; k <= pow2; k <<= 1) {
-            for (int j = k >> 1; j >= kSortTile; j >>= 1)
-                hipLaunchKernelGGL(sort_global_kernel, dim3((pow2 / 2 + 255) / 256, count),
-                                   dim3(256), 0, stream, L, k, j);
-            hipLaunchKernelGGL(sort_tile_kernel, dim3(tiles, count), dim3(1024), 0, stream, L, k,
-                               k);
-        }
+        const int tiles = (m + kSortTile - 1) / kSortTile;
+        if (tiles * kSortTile > pow2) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(sort_tile_kernel, dim3(tiles, count), dim3(1024), 0, stream, L);
+        hipLaunchKernelGGL(sort_rank_kernel, dim3(tiles * (kSortTile / 256), count), dim3(256), 0,
+                           stream, L, tiles);
     }
     hipLaunchKernelGGL(select_kernel, dim3(1, count), dim3(select_threads(pow2)), lds, stream, L);
     return hipGetLastError();

@@ -123,6 +123,7 @@ struct SelectArgs {
     const int32_t *deg;
     const uint16_t *adj;
     uint64_t *keys_g;        // [pow2] global scratch (when not in LDS)
+    uint16_t *order;         // [m] candidates in key order (likewise)
     int32_t *acc;            // [p] out
     int32_t *pos;            // [m] out: -1 (the fill; gather sets accepted ones)
     int32_t p, m, ld, nv, pow2, keys_in_lds, gen_fixed;
@@ -210,8 +211,8 @@ hipError_t launch_pack(const ArgList &L, int count, size_t max_threads, hipStrea
 hipError_t launch_dist(const ArgList &L, int count, long units, int B, int rows,
                        hipStream_t stream);
 hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream);
-hipError_t launch_select(const ArgList &L, int count, size_t lds, int pow2, bool keys_in_lds,
-                         hipStream_t stream);
+hipError_t launch_select(const ArgList &L, int count, size_t lds, int m, int pow2,
+                         bool keys_in_lds, hipStream_t stream);
 size_t select_lds_bytes(int m, int pow2, bool keys_in_lds);
 hipError_t launch_gather(const ArgList &L, int count, int p, hipStream_t stream);
 hipError_t launch_hash(const ArgList &L, int count, int p, int hsize, hipStream_t stream);

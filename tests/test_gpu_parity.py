@@ -297,6 +297,26 @@ def test_select_parity(torch_cuda, oracle_mod, p, gen_no, seed, global_sort):
     np.testing.assert_array_equal(_np(acc), acc_o)
 
 
+@pytest.mark.parametrize("p", [2049, 3071, 3072, 4096, 5001])
+def test_select_sort_tiles(torch_cuda, oracle_mod, p):
+    """Keys sorted in tiles of 2048: 2p at a tile's edges, a last tile of two
+    keys, of all but two and none short; f equal in long runs."""
+    g = gen.random_greedy(12, 0.6, 7)
+    _say(f"select sort tiles p={p}")
+    s = P.Solver(g, select_global_sort=1)
+    I = oracle_mod.Instance(g)
+    rng = np.random.default_rng(p)
+    X = rng.integers(0, 5, size=(2 * p, I.nv), dtype=np.uint8)
+    X[rng.integers(0, 2 * p, size=p)] = X[rng.integers(0, 2 * p, size=p)]
+    Do = oracle_mod.distances(X, X)
+    f = np.sort(rng.integers(0, 9, size=2 * p)).astype(np.int32)
+    import torch
+    acc = s.stage_select(torch.from_numpy(f).cuda(), torch.from_numpy(Do.astype(np.int16)).cuda(),
+                         3, p)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(_np(acc), oracle_mod.select(I.nv, p, 10, p, 3, f, Do))
+
+
 @pytest.mark.parametrize("p,seed", [(2, 1), (24, 2), (130, 3), (513, 4)])
 def test_match_parity(torch_cuda, oracle_mod, p, seed):
     _say(f"match p={p}")
