@@ -739,9 +739,9 @@ __global__ void hash_insert_kernel(const ArgList L) {
 // load, each made the key d << 16 | j (j < 2^15) whose minimum names the
 // partner.  Excluded entries (the history, and the individual itself) are bits
 // in the row's order, one byte per load, so that the loop has four operations
-// an entry and no further lookup.  Bound by the reads of D: 16384 rows of 16384
-// take 125 us (4.3 TB/s); two-byte loads, 64-bit keys and a lookup per entry
-// took 410 us.
+// an entry and no further lookup.  Bound by the reads of D, four loads of a lane
+// in flight: 16384 rows of 16384 take 106 us (5.1 TB/s), one load after another
+// 125; two-byte loads, 64-bit keys and a lookup per entry took 410.
 template <bool IDX>
 __device__ __forceinline__ uint32_t nearest(const MatchArgs &a, const int16_t *row,
                                             const uint32_t *excl) {
@@ -749,23 +749,40 @@ __device__ __forceinline__ uint32_t nearest(const MatchArgs &a, const int16_t *r
     const int cnt = IDX ? a.m : a.p;
     const uint8_t *ex8 = reinterpret_cast<const uint8_t *>(excl);
     uint32_t lb = 0xFFFFFFFFu;
-#pragma unroll 4
-    for (int x0 = lane * 8; x0 + 8 <= cnt; x0 += 512) {
-        const u32x4 q = gload4_any(row + x0);
-        const uint32_t ex = ex8[x0 >> 3];
-        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
-        u32x4 pa = {0u, 0u, 0u, 0u}, pb = pa;
-        if constexpr (IDX) pa = gload4(a.pos + x0), pb = gload4(a.pos + x0 + 4);
-        const uint32_t js[8] = {pa.x, pa.y, pa.z, pa.w, pb.x, pb.y, pb.z, pb.w};
+    struct Eight {
+        u32x4 d, pa, pb;
+        uint32_t ex;
+    };
+    auto load = [&](int x0) {
+        Eight e{gload4_any(row + x0), {0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}, ex8[x0 >> 3]};
+        if constexpr (IDX) e.pa = gload4(a.pos + x0), e.pb = gload4(a.pos + x0 + 4);
+        return e;
+    };
+    auto scan = [&](int x0, const Eight &e) {
+        const uint32_t w[4] = {e.d.x, e.d.y, e.d.z, e.d.w};
+        const uint32_t js[8] = {e.pa.x, e.pa.y, e.pa.z, e.pa.w, e.pb.x, e.pb.y, e.pb.z, e.pb.w};
 #pragma unroll
         for (int t = 0; t < 8; ++t) {
             // pos is -1 for candidates not selected: a key of ~0
             const uint32_t j = IDX ? js[t] : (uint32_t)(x0 + t);
             const uint32_t d = (t & 1) ? w[t >> 1] & 0xFFFF0000u : w[t >> 1] << 16;
-            const uint32_t out = (uint32_t)((int32_t)(ex << (31 - t)) >> 31);
+            const uint32_t out = (uint32_t)((int32_t)(e.ex << (31 - t)) >> 31);
             lb = min(lb, d | j | out);
         }
+    };
+    // loads of D in flight per lane (two beside the map's: with four, 122 registers
+    // leave too few waves, and short rows lose 6 %)
+    constexpr int kAhead = IDX ? 2 : 4;
+    int x0 = lane * 8;
+    for (; x0 - lane * 8 + 512 * kAhead <= cnt; x0 += 512 * kAhead) {
+        Eight e[kAhead];
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) e[h] = load(x0 + 512 * h);
+#pragma unroll
+        for (int h = 0; h < kAhead; ++h) scan(x0 + 512 * h, e[h]);
     }
+#pragma unroll 4
+    for (; x0 + 8 <= cnt; x0 += 512) scan(x0, load(x0));
     const int x = (cnt & ~7) + lane;
     if (x < cnt && !((excl[x >> 5] >> (x & 31)) & 1u)) {
         const uint32_t j = IDX ? (uint32_t)*gptr(a.pos + x) : (uint32_t)x;

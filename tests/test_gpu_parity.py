@@ -930,6 +930,13 @@ def test_select_windows(torch_cuda, oracle_mod, p, group, symmetric, global_sort
 
 
 # --- rows of distances of every length: 16-byte loads, remainders, unaligned rows -----------
+@pytest.mark.parametrize("p", [2039, 2048, 2055, 2056, 4103])
+def test_match_row_passes(torch_cuda, oracle_mod, p):
+    """Rows at the edges of a pass of 2048 entries: one eight short of it, whole,
+    a remainder or eight entries over, and two passes."""
+    test_match_row_lengths(torch_cuda, oracle_mod, p)
+
+
 @pytest.mark.parametrize("p", [2, 3, 5, 7, 9, 17, 513, 1031])
 def test_match_row_lengths(torch_cuda, oracle_mod, p):
     """Stage matching on rows that are no multiple of eight (and start at odd
