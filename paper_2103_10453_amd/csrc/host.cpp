@@ -185,28 +185,50 @@ int max_lds_per_block() { return g_lds_limit; }
 // Candidate positions per lane in PLITS: the chunk size CH that minimises the
 // modelled work of an iteration.  Its eligible vertices, 8 + |V| / 8 (6 to 22 at
 // orders 8 to 30, 24 of 1250 at n = 50, half prefilled, 145 of 1470 at n = 70,
-// 70 %), have chunks for at least one pass of 64 lanes, and a pass costs CH
-// moves plus 4.5 of their like for a chunk's fixed part.  So the smallest
-// instances, where one pass is the least there is, take chunks of 2 or 4: n = 10,
-// 40 %: 1.78 us an iteration of a lone search, 2.00 with 8; n = 16, 40 %: 1.81
-// with 4, 1.98 with 8; from n = 30 on few passes of 8 are better (n = 70, 70 %:
-// 2.7 ns an iteration over the device with 8, 3.3 with 4), except where domains
-// are small (n = 70, 80 %, PartialCol: 1.67 with 4, 1.96 with 8).
-int choose_spl(const plse_instance *h) {
-    if (h->spl) return h->spl;
+// 70 %), have at least `least` chunks, and a pass of them costs CH moves plus 3
+// of their like for a chunk's fixed part.
+int cheapest_chunk(const plse_instance *h, double least) {
     int pick = 4;
     double best = 0.0;
     for (int ch : {2, 4, 8}) {
         double chunks = 0.0;
         for (int v = 0; v < h->nv; ++v) chunks += (double)((((h->vinfo[v] >> 16) & 0xFFu) + ch) / ch);
         const double per_vertex = h->nv ? chunks / h->nv : 0.0;
-        const double cost = std::max(64.0, (8.0 + h->nv / 8.0) * per_vertex) * (ch + 4.5);
+        const double cost = std::max(least, (8.0 + h->nv / 8.0) * per_vertex) * (ch + 3.0);
         if (ch == 2 || cost < best) {
             best = cost;
             pick = ch;
         }
     }
     return pick;
+}
+
+// With the global tabu table a pass of 64 lanes is the least there is, so the
+// smallest instances take chunks of 2 or 4: n = 10, 40 %: 1.78 us an iteration of
+// a lone search, 2.00 with 8; n = 16, 40 %: 1.81 with 4, 1.98 with 8.  From
+// n = 30 on few passes of 8 are better (n = 70, 70 %: 2.7 ns an iteration over
+// the device with 8, 3.3 with 4), except where domains are small (n = 70, 80 %,
+// PartialCol: 1.67 with 4, 1.96 with 8; n = 90, 80 %, 60 iterations from the
+// initial population: 4 takes 1.59 ms, 8 1.76).
+int table_chunk(const plse_instance *h) { return cheapest_chunk(h, 64.0); }
+
+// The LDS-resident kernel deals every iteration and keeps 16 waves of chunks of 2
+// or 4 a CU to 12 of chunks of 8.  4096 searches of 1200 iterations, ms, chunks of
+// 2 | 4 | 8: n = 20, 60 % (|V| = 159): 4.6 | 4.2 | 6.5; n = 24, 40 % (346): 5.6 |
+// 5.2 | 7.6; n = 32, 30 % (717): 15.2 | 12.8 | 11.1; n = 40, 70 %: 8.4 | 7.8 |
+// 11.7; n = 90, 80 %: 65 | 59 | 69.  256 of 2500: n = 16, 40 %: 5.4 | 5.7 | 6.3.
+int lean_chunk(const plse_instance *h) {
+    if (h->nv <= 128) return 2;
+    const int ch = cheapest_chunk(h, 0.0);
+    return h->nv <= 352 ? std::min(ch, 4) : ch;
+}
+
+bool lean_fits(const plse_instance *h, int ch);
+
+int choose_spl(const plse_instance *h) {
+    if (h->spl) return h->spl;
+    const int ch = lean_chunk(h);
+    return lean_fits(h, ch) ? ch : table_chunk(h);
 }
 
 // PLITS per-wave LDS: S, row/column colour counts, eligibility bitmap,
@@ -252,14 +274,17 @@ PlitsLds plits_lean_layout(const plse_instance *h, int ch) {
     return L;
 }
 
+// The LDS-resident kernel was asked for and takes this instance.
+bool lean_fits(const plse_instance *h, int ch) {
+    return h->P.variant == 0 && h->kernel == 2 && h->nv < 65536 &&
+           plits_lean_layout(h, ch).per_wave <= max_lds_per_block();
+}
+
 PlitsLds plits_lds(const plse_instance *h) {
     PlitsLds L;
     const int W = (h->nv + 31) / 32;
     const int ch = choose_spl(h);
-    if (h->P.variant == 0 && h->kernel == 2 && h->nv < 65536) {
-        const PlitsLds Ln = plits_lean_layout(h, ch);
-        if (Ln.per_wave <= max_lds_per_block()) return Ln;
-    }
+    if (lean_fits(h, ch)) return plits_lean_layout(h, ch);
     const int qcap = 64 * ((h->dmax + ch) / ch);  // 64 vertices' chunks
     L.off_h = h->stride;
     L.off_bm = L.off_h + (int)round_up((size_t)2 * h->n * (h->n + 1), 16);
