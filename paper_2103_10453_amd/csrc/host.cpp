@@ -48,10 +48,9 @@ long units_below(int cols, int m) { return dist_units(cols / kDistCols, unit_row
 long all_units(int cols, int m) { return units_below(cols + kDistCols - 1, m); }
 
 // Distance units among P_t (rows 0..p-1 of 2p) that run beside the searches:
-// the whole column blocks, or, of the first alone, what P_t has of it.
-long old_units(int p) {
-    return p < 64 ? 0 : p < kDistCols ? all_units(p, 2 * p) : units_below(p, 2 * p);
-}
+// whole column blocks (none below 128 rows: part of the first block would be
+// computed again with the rest after the searches).
+long old_units(int p) { return units_below(p, 2 * p); }
 
 // Bits needed for colours 0..n.
 int colour_bits(int n) {
@@ -78,7 +77,7 @@ struct ArgBlock {
     InitArgs init;
     BestArgs best;
     PackArgs pack, pack_t;  // rows of P' (after the search), of P_t (beside it)
-    DistArgs dist, dist_t;  // tiles involving P', tiles within P_t
+    DistArgs dist, dist_t;  // units involving P', units within P_t
     CloseArgs close;
     SelectArgs select;
     GatherArgs gather;
@@ -528,7 +527,7 @@ void build_pipeline_args(plse_instance *h, int p, uint64_t seed) {
     // distances among P_t (rows 0..p-1) need nothing from this generation's
     // searches, so they are packed and computed beside them; the rest after
     const int B = colour_bits(h->n);
-    // (with none among P_t, p < 64, the rest packs all 2p rows)
+    // (with none among P_t, p < 128, the rest packs all 2p rows)
     const bool split = old_units(p) > 0;
     uint32_t *planes = at<uint32_t>(h, L.planes);
     A.pack_t = PackArgs{ctl, S_all, planes, p, h->nv, st, W, B, 0, m};
