@@ -270,8 +270,9 @@ int plse_resume(plse_handle h, int32_t population, void *stream, const void *buf
  *
  * Every generation of Alg. 2 runs for all instances together: one launch per
  * kernel covers the instances (grouped by PLITS launch shape and by colour
- * width, longest estimated work first), captured once as HIP graphs and
- * replayed per generation.  Each handle needs its own attached workspace of
+ * width, longest estimated work first).  The groups' searches run on streams
+ * forked from and joined back into `stream`; a batch captures no graphs.  Each
+ * handle needs its own attached workspace of
  * plse_workspace_bytes(hs[i], population); the handles must be distinct and
  * idle.  seeds[i], best_grids[i] (host n_i*n_i) and filled[i] belong to
  * hs[i].  The result of each instance is identical to plse_solve of that

@@ -607,7 +607,9 @@ struct Session {
     int base = 0;   // generations run before it (a session resumed from a checkpoint)
     uint64_t seed = 0;  // single-instance sessions
     std::vector<PlitsGroup> groups;  // largest estimated work first
-    hipGraphExec_t ls = nullptr, rest = nullptr;  // a generation's searches; the rest
+    // a generation's searches; the rest (one instance; several are enqueued
+    // kernel by kernel)
+    hipGraphExec_t ls = nullptr, rest = nullptr;
     std::vector<hipEvent_t> ev;                   // 3 per generation
     bool staged = false;                          // stage timing: kStages + 1 events per generation
     std::vector<hipEvent_t> sev;
@@ -676,8 +678,9 @@ int device_cus() {
 }
 
 // One generation's tabu searches.  Several groups run concurrently: group 0
-// on `s`, the others on side streams forked from and joined back into `s`
-// (captured, they become the parallel branches of the generation's graph).
+// on `s`, the others on side streams forked from and joined back into `s` (not
+// under capture: the fork's events and side streams would take part in it and
+// outlive the stream that is captured).
 int enqueue_local_search(Session &S, hipStream_t s) {
     RC_TRY(launch_ctl(S.hs, false, s));
     if (S.groups.size() == 1) return launch_group(S, S.groups[0], s);
@@ -870,13 +873,14 @@ void shape_session(Session &S) {
 int session_begin(Session &S, const uint64_t *seeds, hipStream_t s) {
     RC_TRY(admit(S.hs, S.p, seeds, s));
     shape_session(S);
-    // a generation's searches are one graph (several groups: forked branches
-    // that run side by side), the rest another
+    S.steps = 0;
     S.staged = S.hs.size() == 1 && S.hs[0]->stage_timing != 0;
-    if (S.staged) {
-        S.steps = 0;
-        return PLSE_OK;  // stages enqueued one by one, each bracketed by events
-    }
+    if (S.staged) return PLSE_OK;  // stages enqueued one by one, each bracketed by events
+    // Several instances are enqueued kernel by kernel, their distances among P_t
+    // in line: a generation's searches take long beside some 40 launches, and
+    // their groups fork side streams, which stay out of captures.
+    if (S.hs.size() > 1) return PLSE_OK;
+    // one instance: the searches are one graph, the rest another
     RC_TRY(capture([&](hipStream_t cs) { return enqueue_local_search(S, cs); }, &S.ls));
     RC_TRY(capture([&](hipStream_t cs) { return enqueue_rest(S, cs); }, &S.rest));
     if (old_units(S.p) > 0) {
@@ -885,7 +889,6 @@ int session_begin(Session &S, const uint64_t *seeds, hipStream_t s) {
         HIP_TRY(hipEventCreateWithFlags(&S.dfork, hipEventDisableTiming));
         HIP_TRY(hipEventCreateWithFlags(&S.djoin, hipEventDisableTiming));
     }
-    S.steps = 0;
     return PLSE_OK;
 }
 
@@ -937,6 +940,8 @@ int session_step(Session &S, int generations, hipStream_t s) {
             HIP_TRY(hipStreamWaitEvent(S.dstream, S.dfork, 0));
             HIP_TRY(hipGraphLaunch(S.dold, S.dstream));
             HIP_TRY(hipEventRecord(S.djoin, S.dstream));
+        } else if (!S.rest && old_units(S.p) > 0) {
+            RC_TRY(enqueue_old_dist(S, s));
         }
         HIP_TRY(hipEventRecord(S.ev[k], s));
         if (S.ls)
@@ -945,7 +950,10 @@ int session_step(Session &S, int generations, hipStream_t s) {
             RC_TRY(enqueue_local_search(S, s));
         HIP_TRY(hipEventRecord(S.ev[k + 1], s));
         if (S.dold) HIP_TRY(hipStreamWaitEvent(s, S.djoin, 0));
-        HIP_TRY(hipGraphLaunch(S.rest, s));
+        if (S.rest)
+            HIP_TRY(hipGraphLaunch(S.rest, s));
+        else
+            RC_TRY(enqueue_rest(S, s));
         if (S.stop_host) {
             plse_instance *h = S.hs[0];
             HIP_TRY(hipMemcpyAsync(S.stop_host + (S.steps + g) % Session::kStopRing,

@@ -35,3 +35,22 @@ def test_solve_around_column_blocks(torch_cuda, oracle_mod, p, depth):
     np.testing.assert_array_equal(grid, r["grid"])
     np.testing.assert_array_equal(st["best_f_per_gen"], r["best_f"][:r["gens"]])
     np.testing.assert_array_equal(st["counters_per_gen"], r["counters"][:r["gens"]])
+
+
+def test_batch_with_distances_of_both_kinds(torch_cuda):
+    """A batch of several search groups whose distances start in two parts
+    equals the instances solved alone."""
+    print("[gpu-case] batch of 5 instances p=130 G=2", flush=True)
+    grids = [gen.random_greedy(12, 0.6, 5), gen.random_greedy(20, 0.5, 7),
+             gen.planted(33, 0.45, 9), gen.random_greedy(45, 0.7, 4), gen.planted(10, 0.4, 0)]
+    p, seeds = 130, [3, 1, 4, 1, 5]
+    kw = [dict(depth=300, variant=int(k == 1)) for k in range(5)]
+    solvers = [P.Solver(g, **k) for g, k in zip(grids, kw)]
+    res = P.Solver.solve_batch(solvers, p, 2, seeds)
+    for g, k, s, seed, (grid, filled) in zip(grids, kw, solvers, seeds, res):
+        alone = P.Solver(g, **k)
+        want, f = alone.solve(p, 2, seed)
+        assert f == filled
+        np.testing.assert_array_equal(grid, want)
+        np.testing.assert_array_equal(s.stats()["counters_per_gen"],
+                                      alone.stats()["counters_per_gen"])

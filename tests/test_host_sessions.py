@@ -38,3 +38,7 @@ def test_single_sessions(check):
 
 def test_distance_units_once(check):
     check("units")
+
+
+def test_batch_sessions(check):
+    check("batch")
