@@ -142,6 +142,7 @@ thread_local std::string g_hip_error;
 int hip_fail(hipError_t e, const char *what = nullptr) {
     g_hip_error = hipGetErrorString(e);
     if (what) g_hip_error += std::string(" in ") + what;
+    (void)hipGetLastError();  // reported: not the next launch's error too
     return PLSE_E_HIP;
 }
 
@@ -1027,6 +1028,13 @@ struct BusyGuard {
     }
 };
 
+// What a failed call has enqueued ends before its session, its workspace or the
+// library's scratch array goes to somebody else.
+int settle(int rc, hipStream_t s) {
+    if (rc) (void)hipStreamSynchronize(s);
+    return rc;
+}
+
 void drop_session(plse_instance *h) {
     delete h->own;
     h->own = nullptr;
@@ -1389,7 +1397,8 @@ int plse_begin(plse_handle h, int32_t p, uint64_t seed, void *stream) {
     S->hs = {h};
     S->p = p;
     S->seed = seed;
-    const int rc = session_begin(*S, &seed, reinterpret_cast<hipStream_t>(stream));
+    const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const int rc = settle(session_begin(*S, &seed, s), s);
     if (rc) {
         delete S;
         return rc;
@@ -1413,7 +1422,8 @@ int plse_end(plse_handle h, void *stream, int8_t *best_grid, int32_t *filled) {
     if (!guard.ok) return PLSE_E_BUSY;
     if (!h->in_session || !h->own) return PLSE_E_ARG;
     int8_t *grids[1] = {best_grid};
-    const int rc = session_end(*h->own, reinterpret_cast<hipStream_t>(stream), {h}, grids, filled);
+    const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+    const int rc = settle(session_end(*h->own, s, {h}, grids, filled), s);
     drop_session(h);
     return rc;
 }
@@ -1555,7 +1565,7 @@ int plse_resume(plse_handle h, int32_t p, void *stream, const void *buf, size_t 
         const hipError_t e = hipStreamSynchronize(s);
         if (e != hipSuccess) rc = hip_fail(e, "plse_resume");
     }
-    if (rc) {
+    if (settle(rc, s)) {
         delete S;
         return rc;
     }
@@ -1603,7 +1613,8 @@ int plse_solve_noalloc(plse_handle h, int32_t p, int32_t G, uint64_t seed, void 
         const size_t keep_bytes = h->ws_bytes;
         h->ws = reinterpret_cast<uint8_t *>(ptr);
         h->ws_bytes = kScratchBytes;
-        rc = solve_direct(h, p, G, seed, reinterpret_cast<hipStream_t>(stream), best_grid, filled);
+        const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+        rc = settle(solve_direct(h, p, G, seed, s, best_grid, filled), s);
         h->ws = keep_ws;
         h->ws_bytes = keep_bytes;
     }
@@ -1677,7 +1688,8 @@ int plse_batch_begin(const plse_handle *hs, int32_t count, int32_t p, const uint
         b->S.p = p;
         b->order.assign(hs, hs + count);
         std::vector<uint64_t> sd(seeds, seeds + count);
-        rc = session_begin(b->S, sd.data(), reinterpret_cast<hipStream_t>(stream));
+        const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
+        rc = settle(session_begin(b->S, sd.data(), s), s);
     }
     if (rc) {
         delete b;
@@ -1702,7 +1714,7 @@ int plse_batch_end(plse_batch b, void *stream, int8_t *const *best_grids, int32_
             rc = session_end(b->S, reinterpret_cast<hipStream_t>(stream), b->order, best_grids,
                              filled);
     }
-    if (rc) (void)hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream));
+    (void)settle(rc, reinterpret_cast<hipStream_t>(stream));
     delete b;
     return rc;
 }
@@ -1734,6 +1746,7 @@ int plse_solve_batch(const plse_handle *hs, int32_t count, int32_t p, int32_t G,
         rc = session_begin(S, sd.data(), s);
         if (!rc) rc = session_step(S, G, s);
         if (!rc) rc = session_end(S, s, order, best_grids, filled);
+        (void)settle(rc, s);
     }
     for (BusyGuard *g : guards) delete g;
     return rc;

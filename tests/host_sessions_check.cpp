@@ -85,8 +85,9 @@ void complain(const std::string &what) {
     if (bad++ < 10) std::fprintf(stderr, "violation: %s\n", what.c_str());
 }
 bool injected() {
-    ++calls;
-    return fail_at != 0 && calls == fail_at;
+    if (++calls != fail_at) return false;
+    last_error = hipErrorOutOfMemory;
+    return true;
 }
 Stream *of(hipStream_t s) {
     if (!s) return &null_stream;
@@ -330,7 +331,7 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
 }
 hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t lds, hipStream_t s) {
     std::lock_guard<std::recursive_mutex> lk(mu);
-    if (injected()) return last_error = hipErrorOutOfMemory;
+    if (injected()) return hipErrorOutOfMemory;
     Stream *p = of(s);
     const std::string &name = kernel_names()[f];
     Launch l{name, g, b, lds, {}};
@@ -515,6 +516,45 @@ void units() {
     }
 }
 
+// The k-th runtime call of a solve fails, for every k: the call reports it,
+// nothing of it runs on or is left over, and the next call knows nothing of it.
+void errors() {
+    const int p = 130;
+    Batch b(p);
+    Inst a(20, 50, p, 3);
+    int32_t f = 0;
+    size_t need = 0;
+    std::vector<uint8_t> img;
+    NEED(plse_begin(a.h, p, 1, nullptr) == PLSE_OK);
+    NEED(plse_checkpoint(a.h, nullptr, nullptr, 0, &need) == PLSE_OK);
+    img.resize(need);
+    NEED(plse_checkpoint(a.h, nullptr, img.data(), need, &need) == PLSE_OK);
+    NEED(plse_end(a.h, nullptr, a.out.data(), &f) == PLSE_OK);
+    for (int kind = 0; kind < 4; ++kind) {
+        bool through = false;
+        for (long k = 1; !through && k < 5000; ++k) {
+            complete(null_stream.pend);
+            calls = 0;
+            fail_at = k;
+            int rc = PLSE_OK;
+            switch (kind) {
+                case 0: rc = plse_solve(a.h, p, 2, 1, nullptr, a.out.data(), &f); break;
+                case 1: rc = plse_solve_noalloc(a.h, p, 2, 1, nullptr, a.out.data(), &f, &need); break;
+                case 2: rc = b.solve(p, 2); break;
+                default: rc = plse_resume(a.h, p, nullptr, img.data(), img.size());
+            }
+            through = calls < k;
+            fail_at = 0;
+            if (kind == 3 && !rc) NEED(plse_end(a.h, nullptr, a.out.data(), &f) == PLSE_OK);
+            const std::string at = "kind " + std::to_string(kind) + ", call " + std::to_string(k);
+            if ((rc == PLSE_E_HIP) == through) complain(at + ": status " + std::to_string(rc));
+            nothing_left(at.c_str());
+            if (bad > 10) return;
+        }
+        NEED(through);
+    }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -522,6 +562,7 @@ int main(int argc, char **argv) {
     if (what == "batch") batch();
     else if (what == "single") single();
     else if (what == "units") units();
+    else if (what == "errors") errors();
     else return std::fprintf(stderr, "no scenario %s\n", what.c_str()), 2;
     if (!bad) std::puts("ok");
     return bad ? 1 : 0;

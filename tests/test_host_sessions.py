@@ -42,3 +42,7 @@ def test_distance_units_once(check):
 
 def test_batch_sessions(check):
     check("batch")
+
+
+def test_failing_calls_settle(check):
+    check("errors")
