@@ -142,9 +142,10 @@ int plse_row_stride(plse_handle h, int32_t *stride);
  *                 restores the caller's value when it ends.
  * Errors: PLSE_E_PARAM.
  */
-/* Test hook (selection): "select_global_sort" 1 sorts the selection keys with
- * the global-memory network even when they would fit in LDS (populations of
- * at least 4096; the network always serves populations whose keys exceed LDS). */
+/* Test hook (selection): "select_global_sort" 1 sorts the selection keys in
+ * global memory, and keeps the candidates' places in their order there, even
+ * when they would fit in LDS (populations above 2048; the sort in global memory
+ * always serves populations whose keys exceed LDS). */
 /* Test hook (serving): "fail_at_generation" g > 0 makes a served request end
  * with PLSE_E_FAULT after its generation g, without touching other requests. */
 int plse_set_param(plse_handle h, const char *key, int64_t value);

@@ -116,7 +116,7 @@ struct plse_instance {
     int persistent = 1;  // batched searches: one persistent launch per group (0: a grid per instance)
     int fail_at = 0;  // serving test hook: end the request after this generation
     int max_gens = PLSE_MAX_GENERATIONS;  // generations a session may run (sizes its records)
-    int sel_global = 0;  // test hook: sort selection keys in global memory when possible
+    int sel_global = 0;  // test hook: selection keys and ranks in global memory when possible
 
     uint8_t *ws = nullptr;
     size_t ws_bytes = 0;
@@ -483,6 +483,7 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
     a.adj = at<uint16_t>(h, L.adj);
     a.keys_g = at<uint64_t>(h, L.keys);
     a.order = at<uint16_t>(h, L.order);
+    a.rank_g = at<uint16_t>(h, L.keys);
     a.acc = acc;
     a.pos = at<int32_t>(h, L.pos);
     a.p = p;
@@ -490,10 +491,15 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
     a.ld = ld;
     a.nv = h->nv;
     a.pow2 = L.pow2_sel;
-    // keys in LDS when they fit; the sort in global memory takes whole tiles
-    // (8192 keys at least)
-    const bool fits = select_lds_bytes(2 * p, L.pow2_sel, true) <= (size_t)max_lds_per_block();
-    a.keys_in_lds = (fits && !(h->sel_global && L.pow2_sel >= 8192)) || L.pow2_sel < 8192 ? 1 : 0;
+    // keys, or at least the places in their order, in LDS when they fit; the sort
+    // in global memory takes whole tiles (8192 keys at least)
+    const bool in_lds = !(h->sel_global && L.pow2_sel >= 8192);
+    auto fits = [&](bool keys) {
+        return in_lds &&
+               select_lds_bytes(2 * p, L.pow2_sel, keys, true) <= (size_t)max_lds_per_block();
+    };
+    a.keys_in_lds = fits(true) || L.pow2_sel < 8192 ? 1 : 0;
+    a.ranks_in_lds = a.keys_in_lds || fits(false) ? 1 : 0;
     a.gen_fixed = gen_fixed;
     a.spacing = h->P.spacing;
     a.seed_lo = (uint32_t)seed;
@@ -502,7 +508,8 @@ SelectArgs make_select(plse_instance *h, int p, int gen_fixed, uint64_t seed, co
 }
 
 size_t select_lds(plse_instance *h, int p) {
-    return select_lds_bytes(2 * p, h->L.pow2_sel, h->args.select.keys_in_lds != 0);
+    const SelectArgs &a = h->args.select;
+    return select_lds_bytes(2 * p, h->L.pow2_sel, a.keys_in_lds != 0, a.ranks_in_lds != 0);
 }
 
 // Argument blocks of the whole pipeline of a solve with population p.
@@ -749,8 +756,9 @@ int enqueue_rest(Session &S, hipStream_t s, hipEvent_t *mark = nullptr) {
     const size_t sl = select_lds(S.hs[0], p);
     const int pow2 = S.hs[0]->L.pow2_sel;
     const bool keys_lds = S.hs[0]->args.select.keys_in_lds != 0;
+    const bool ranks_lds = S.hs[0]->args.select.ranks_in_lds != 0;
     RC_TRY(launch_over(S.hs, &ArgBlock::select, [&](const ArgList &L, int c) {
-        return launch_select(L, c, sl, m, pow2, keys_lds, s);
+        return launch_select(L, c, sl, m, pow2, keys_lds, ranks_lds, s);
     }));
     RC_TRY(launch_over(S.hs, &ArgBlock::gather,
                        [&](const ArgList &L, int c) { return launch_gather(L, c, p, s); }));
@@ -1970,7 +1978,7 @@ int plse_stage_select(plse_handle h, int32_t p, int32_t gen, uint64_t seed, void
     RC_TRY(upload_args(h, s));
     HIP_TRY(launch_close(single(h, &ArgBlock::close), 1, m, s));
     HIP_TRY(launch_select(single(h, &ArgBlock::select), 1, select_lds(h, p), 2 * p, h->L.pow2_sel,
-                          h->args.select.keys_in_lds != 0, s));
+                          h->args.select.keys_in_lds != 0, h->args.select.ranks_in_lds != 0, s));
     return PLSE_OK;
 }
 

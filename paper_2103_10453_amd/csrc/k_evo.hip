@@ -457,10 +457,18 @@ __global__ __launch_bounds__(256) void sort_rank_kernel(const ArgList L, int til
 // families of about eight: 178 us with the keys sorted before; one wave that
 // decided 64 candidates at a time, one after the other in a scalar loop, took
 // 2.92 ms.  128 candidates: 11.5 us with their sort, from 17.5.
+__host__ __device__ inline size_t select_head_bytes(int m, int pow2, bool keys, bool ranks) {
+    return ((keys ? (size_t)pow2 * 8 : ranks ? (size_t)m * 2 : 0) + 15) & ~(size_t)15;
+}
+
 __device__ __forceinline__ bool is_close(const SelectArgs &a, int16_t d) {
     return a.spacing * (int64_t)d <= (int64_t)a.nv;
 }
 
+// Each candidate's place is read per member of a close list: from LDS, or from
+// the workspace where LDS is limited to 64 KiB and more than 27900 candidates
+// leave no room for them.
+template <bool RANK_LDS>
 __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
     extern __shared__ __align__(16) uint8_t lds[];
     __shared__ int s_stop[2], s_any[2], s_na;
@@ -473,12 +481,12 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
     const int nbw = (m + 31) / 32;
     const bool klds = a.keys_in_lds != 0;
     // keys (then the candidates in order, and each candidate's place in it);
-    // with the order in global memory the places alone
+    // with the order in global memory the places alone, or nothing
     uint64_t *K = reinterpret_cast<uint64_t *>(lds);
     uint16_t *rank = reinterpret_cast<uint16_t *>(lds);
     uint16_t *order = rank + P2;
-    uint32_t *blocked = reinterpret_cast<uint32_t *>(
-        lds + (((klds ? (size_t)P2 * 8 : (size_t)m * 2) + 15) & ~(size_t)15));
+    uint32_t *blocked = reinterpret_cast<uint32_t *>(lds + select_head_bytes(m, P2, klds, RANK_LDS));
+    auto rank_at = [&](int y) -> int { return RANK_LDS ? (int)rank[y] : (int)*gptr(a.rank_g + y); };
     uint32_t *accb = blocked + nbw;  // accepted, by place
     uint32_t *gpre = accb + nbw;     // accepted before each group of 64 places
 
@@ -521,8 +529,13 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
             }
         }
     } else {
-        for (int r = tid; r < m; r += nthr)
-            rank[*gptr(a.order + r)] = (uint16_t)r;
+        for (int r = tid; r < m; r += nthr) {
+            const int x = *gptr(a.order + r);
+            if constexpr (RANK_LDS)
+                rank[x] = (uint16_t)r;
+            else
+                *gptr(a.rank_g + x) = (uint16_t)r;
+        }
     }
     __syncthreads();
     auto order_at = [&](int r) -> int {
@@ -583,7 +596,7 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
                 for (int t = 0; t < 8; ++t) {
                     const int y = (int)((ew[t >> 1] >> (16 * (t & 1))) & 0xFFFFu);
                     if (q0 + t < d) {
-                        const int ry = rank[y];
+                        const int ry = rank_at(y);
                         if (ry > r) fn(y, ry);
                     }
                 }
@@ -645,9 +658,9 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
 // Threads: a window each, and half the keys of the sort.
 static int select_threads(int pow2) { return std::min(1024, std::max(64, pow2 / 2)); }
 
-size_t select_lds_bytes(int m, int pow2, bool keys_in_lds) {
-    const size_t keys = ((keys_in_lds ? (size_t)pow2 * 8 : (size_t)m * 2) + 15) & ~(size_t)15;
-    return keys + ((size_t)2 * ((m + 31) / 32) + (size_t)(m + 63) / 64) * 4;
+size_t select_lds_bytes(int m, int pow2, bool keys_in_lds, bool ranks_in_lds) {
+    return select_head_bytes(m, pow2, keys_in_lds, ranks_in_lds) +
+           ((size_t)2 * ((m + 31) / 32) + (size_t)(m + 63) / 64) * 4;
 }
 
 // New population P_{t+1} = accepted candidates in acceptance order: rows,
@@ -960,7 +973,7 @@ hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream) 
 }
 
 hipError_t launch_select(const ArgList &L, int count, size_t lds, int m, int pow2,
-                         bool keys_in_lds, hipStream_t stream) {
+                         bool keys_in_lds, bool ranks_in_lds, hipStream_t stream) {
     if (!keys_in_lds) {
         const int tiles = (m + kSortTile - 1) / kSortTile;
         if (tiles * kSortTile > pow2) return hipErrorInvalidValue;
@@ -968,7 +981,8 @@ hipError_t launch_select(const ArgList &L, int count, size_t lds, int m, int pow
         hipLaunchKernelGGL(sort_rank_kernel, dim3(tiles * (kSortTile / 256), count), dim3(256), 0,
                            stream, L, tiles);
     }
-    hipLaunchKernelGGL(select_kernel, dim3(1, count), dim3(select_threads(pow2)), lds, stream, L);
+    void (*k)(const ArgList) = ranks_in_lds ? select_kernel<true> : select_kernel<false>;
+    hipLaunchKernelGGL(k, dim3(1, count), dim3(select_threads(pow2)), lds, stream, L);
     return hipGetLastError();
 }
 
@@ -997,7 +1011,7 @@ hipError_t launch_aux(const ArgList &L, int count, int p, hipStream_t stream) {
 }
 
 hipError_t evo_set_lds_limit(int bytes) {
-    hipError_t e = set_dynamic_lds_limit((const void *)select_kernel, bytes);
+    hipError_t e = set_dynamic_lds_limit((const void *)select_kernel<true>, bytes);
     if (e != hipSuccess) return e;
     return set_dynamic_lds_limit((const void *)match_kernel, bytes);
 }

@@ -124,9 +124,10 @@ struct SelectArgs {
     const uint16_t *adj;
     uint64_t *keys_g;        // [pow2] global scratch (when not in LDS)
     uint16_t *order;         // [m] candidates in key order (likewise)
+    uint16_t *rank_g;        // [m] places in that order (when not in LDS; the sorted keys' memory)
     int32_t *acc;            // [p] out
     int32_t *pos;            // [m] out: -1 (the fill; gather sets accepted ones)
-    int32_t p, m, ld, nv, pow2, keys_in_lds, gen_fixed;
+    int32_t p, m, ld, nv, pow2, keys_in_lds, ranks_in_lds, gen_fixed;
     int64_t spacing;
     uint32_t seed_lo, seed_hi;
 };
@@ -212,8 +213,8 @@ hipError_t launch_dist(const ArgList &L, int count, long units, int B, int rows,
                        hipStream_t stream);
 hipError_t launch_close(const ArgList &L, int count, int m, hipStream_t stream);
 hipError_t launch_select(const ArgList &L, int count, size_t lds, int m, int pow2,
-                         bool keys_in_lds, hipStream_t stream);
-size_t select_lds_bytes(int m, int pow2, bool keys_in_lds);
+                         bool keys_in_lds, bool ranks_in_lds, hipStream_t stream);
+size_t select_lds_bytes(int m, int pow2, bool keys_in_lds, bool ranks_in_lds);
 hipError_t launch_gather(const ArgList &L, int count, int p, hipStream_t stream);
 hipError_t launch_hash(const ArgList &L, int count, int p, int hsize, hipStream_t stream);
 hipError_t launch_match(const ArgList &L, int count, int p, int cnt, hipStream_t stream);  // cnt: row entries read

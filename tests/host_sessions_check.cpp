@@ -555,6 +555,23 @@ void errors() {
     }
 }
 
+// Where the runtime refuses more than 64 KiB of dynamic LDS, every launch stays
+// within: populations up to the largest whose distances fit a device.
+void lds64() {
+    refuse_lds = true;
+    lds_limit = 65536;
+    for (int p : {2, 64, 2048, 3584, 4096, 5000, 8192, 12000, 16384, 32768})
+        for (int hook : {0, 1}) {
+            Inst a(6, 50, p, 3);
+            int32_t f = 0;
+            NEED(plse_set_param(a.h, "select_global_sort", hook) == PLSE_OK);
+            const int before = bad;
+            NEED(plse_solve(a.h, p, 1, 1, nullptr, a.out.data(), &f) == PLSE_OK);
+            if (bad != before) std::fprintf(stderr, "  population %d, hook %d\n", p, hook);
+            nothing_left("64 KiB");
+        }
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -563,6 +580,7 @@ int main(int argc, char **argv) {
     else if (what == "single") single();
     else if (what == "units") units();
     else if (what == "errors") errors();
+    else if (what == "lds64") lds64();
     else return std::fprintf(stderr, "no scenario %s\n", what.c_str()), 2;
     if (!bad) std::puts("ok");
     return bad ? 1 : 0;

@@ -46,3 +46,7 @@ def test_batch_sessions(check):
 
 def test_failing_calls_settle(check):
     check("errors")
+
+
+def test_launches_within_64k_lds(check):
+    check("lds64")
