@@ -567,9 +567,9 @@ __global__ __launch_bounds__(1024) void select_kernel(const ArgList L) {
             auto mark = [&](int y, int16_t dist) {
                 if (y != x0 && is_close(a, dist)) atomicOr(&blocked[y >> 5], 1u << (y & 31));
             };
-            if ((a.ld & 7) == 0 && (m & 7) == 0) {
+            if ((m & 7) == 0) {
                 for (int y = 8 * tid; y < m; y += 8 * nthr) {
-                    const u32x4 q = gload4(row + y);
+                    const u32x4 q = gload4_any(row + y);
                     const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
                     for (int t = 0; t < 8; ++t)
