@@ -149,15 +149,6 @@ __device__ __forceinline__ uint32_t rank_below(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-__device__ __forceinline__ uint32_t shfl_u32(uint32_t v, int src) {
-    return (uint32_t)__shfl((int)v, src, 64);
-}
-
-__device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
-    const uint32_t lo = shfl_u32((uint32_t)v, src), hi = shfl_u32((uint32_t)(v >> 32), src);
-    return ((uint64_t)hi << 32) | lo;
-}
-
 __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
     const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
     const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
@@ -188,25 +179,6 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v) {
     return v;
 }
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += (uint32_t)__shfl_xor((int)v, m, 64);
-    return v;
-}
-
-// Exclusive prefix sum over the wave; *total receives the wave sum.
-__device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t *total) {
-    const int lane = lane_id();
-    uint32_t x = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)x, d, 64);
-        if (lane >= d) x += o;
-    }
-    *total = shfl_u32(x, 63);
-    return x - v;
-}
-
 __device__ __forceinline__ int readfirst(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // ---------------------------------------------------------------------------
@@ -234,27 +206,6 @@ __device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
 
 __device__ __forceinline__ uint32_t readlane_u32(uint32_t v, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
-}
-
-template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ void dpp_min_step(uint32_t &hi, uint32_t &lo) {
-    const uint32_t oh = dpp_u32<CTRL, ROW_MASK>(hi, hi);
-    const uint32_t ol = dpp_u32<CTRL, ROW_MASK>(lo, lo);
-    const bool take = (oh < hi) || (oh == hi && ol < lo);
-    hi = take ? oh : hi;
-    lo = take ? ol : lo;
-}
-
-// Wave minimum of a 64-bit key, returned uniformly to all lanes.
-__device__ __forceinline__ uint64_t wave_min_u64_dpp(uint64_t v) {
-    uint32_t hi = (uint32_t)(v >> 32), lo = (uint32_t)v;
-    dpp_min_step<DPP_QUAD_1032, 0xF>(hi, lo);
-    dpp_min_step<DPP_QUAD_2301, 0xF>(hi, lo);
-    dpp_min_step<DPP_ROW_HALF_MIRROR, 0xF>(hi, lo);
-    dpp_min_step<DPP_ROW_MIRROR, 0xF>(hi, lo);
-    dpp_min_step<DPP_ROW_BCAST15, 0xA>(hi, lo);
-    dpp_min_step<DPP_ROW_BCAST31, 0xC>(hi, lo);
-    return ((uint64_t)readlane_u32(hi, 63) << 32) | readlane_u32(lo, 63);
 }
 
 // Wave minimum (u32), returned uniformly.

@@ -1,5 +1,5 @@
 // k_evo.hip -- the per-generation kernels around the tabu search on gfx950:
-// best-solution saving, Hamming distances (Eq. 8) as bit-sliced tiles, the
+// best-solution saving, bit-sliced Hamming distances (Eq. 8), the
 // population update (Alg. 4), nearest-neighbour parent matching
 // (Section 3.5.1) and the AUX crossover (Alg. 5, Eq. 9), plus the small
 // control kernels of the generation graph.
@@ -284,7 +284,6 @@ __global__ __launch_bounds__(256) void dist_kernel(const ArgList L) {
     }
 }
 
-
 // ---------------------------------------------------------------------------
 // Population update (Alg. 4)
 // ---------------------------------------------------------------------------
@@ -350,7 +349,6 @@ __global__ __launch_bounds__(256) void close_kernel(const ArgList L) {
     cnt += (uint32_t)__popcll(msk);
     if (lane == 0) *gptr(a.deg + x) = (int32_t)cnt;
 }
-
 
 // Selection keys of P^all: f << 48 | SELECT draw << 16 | index (the order of
 // Alg. 4: e, then a random key, then the index), ~0 beyond m: the four from 4q on.
@@ -705,7 +703,6 @@ __global__ __launch_bounds__(256) void copyback_kernel(const ArgList L) {
     }
 }
 
-
 // ---------------------------------------------------------------------------
 // Parent matching (Section 3.5.1): nearest neighbour (D, then slot) among the
 // individuals not yet crossed with S_i; plain nearest neighbour when all are.
@@ -717,7 +714,6 @@ __device__ __forceinline__ uint32_t hash_uid(uint64_t u) {
     u ^= u >> 33;
     return (uint32_t)u;
 }
-
 
 // Words of an individual's bits of excluded entries of its row.
 __host__ __device__ inline int match_words(int cnt) { return (cnt + 31) / 32; }
@@ -746,7 +742,6 @@ __global__ void hash_insert_kernel(const ArgList L) {
         h = (h + 1) & (uint32_t)(a.hsize - 1);
     }
 }
-
 
 // One wave per individual.  Its row of D is read eight distances a lane and
 // load, each made the key d << 16 | j (j < 2^15) whose minimum names the
@@ -865,7 +860,6 @@ __global__ __launch_bounds__(256) void match_kernel(const ArgList L) {
     }
 }
 
-
 // ---------------------------------------------------------------------------
 // AUX crossover (Alg. 5): vertex v keeps S_i(v) when its XOVER draw is below
 // thr = floor((beta*D - |V|) 2^32 / (beta*D)) (p_ij of Eq. 9 in 2^-32
@@ -913,11 +907,6 @@ __global__ __launch_bounds__(256) void aux_kernel(const ArgList L) {
         so[q] = out;
     }
 }
-
-
-
-
-
 
 hipError_t launch_ctl_reset(const ArgList &L, int count, hipStream_t stream) {
     hipLaunchKernelGGL(ctl_reset_kernel, dim3(1, count), dim3(64), 0, stream, L);

@@ -57,3 +57,11 @@ def test_lds_resident_kernel_has_no_calls_and_no_scratch(tmp_path):
     for name, (body, scratch) in lean.items():
         assert "s_swappc" not in body, name + " calls a function"
         assert scratch == 0, (name, scratch)
+
+
+def test_batched_search_kernels_have_no_scratch(tmp_path):
+    funcs = _kernels("k_plits.hip", tmp_path)
+    persistent = {k: v for k, v in funcs.items() if "plits_persistent" in k}
+    assert len(persistent) == 6, sorted(persistent)
+    for name, (body, scratch) in persistent.items():
+        assert scratch == 0, (name, scratch)
