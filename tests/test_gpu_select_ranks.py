@@ -62,3 +62,61 @@ def test_select_shifted_rows(torch_cuda, oracle_mod, p, shift):
     torch.cuda.synchronize()
     want = oracle_mod.select(nv, p, 10, 77, 3, f, D.astype(np.int32))
     np.testing.assert_array_equal(acc.cpu().numpy(), want)
+
+
+def _chain(m, width):
+    """Candidates in key order (f ascending), each close to the next `width`."""
+    D = np.full((m, m), 50, dtype=np.int16)
+    for k in range(1, width + 1):
+        i = np.arange(m - k)
+        D[i, i + k] = D[i + k, i] = 3
+    np.fill_diagonal(D, 0)
+    return D
+
+
+@pytest.mark.parametrize("p,width,step,hook", [
+    (5, 1, 1, 0), (12, 1, 1, 0), (16, 13, 1, 0), (32, 1, 1, 0),   # six rounds and fewer
+    (33, 2, 1, 0), (100, 13, 1, 0), (700, 1, 1, 0), (1500, 5, 3, 0),
+    (1500, 16, 1, 0),                                             # lists of 32, all that are kept
+    (1500, 20, 1, 0),                                             # longer ones between them
+    (2100, 1, 1, 1), (2100, 7, 40, 1),
+])
+def test_select_chains(torch_cuda, oracle_mod, p, width, step, hook):
+    """Chains of close candidates as long as the population, in key order or
+    (steps of f) broken by the draws."""
+    torch = torch_cuda
+    print(f"[gpu-case] select chain p={p} width={width} step={step} hook={hook}", flush=True)
+    s = P.Solver(gen.random_greedy(12, 0.6, 7), select_global_sort=hook)
+    m = 2 * p
+    D = _chain(m, width)
+    f = (np.arange(m) // step).astype(np.int32)
+    acc = s.stage_select(torch.from_numpy(f).cuda(), torch.from_numpy(D).cuda(), 3, 77)
+    torch.cuda.synchronize()
+    want = oracle_mod.select(s.nv, p, 10, 77, 3, f, D.astype(np.int32))
+    np.testing.assert_array_equal(acc.cpu().numpy(), want)
+
+
+def test_select_chain_time(torch_cuda):
+    """One wave decides 64 candidates in 6 us: 128 times that for 8192 in one
+    chain, six times the selection of candidates far apart (128 us); twice
+    that is allowed.  Rounds as long as the chain took 34 times."""
+    torch = torch_cuda
+    p = 4096
+    s = P.Solver(gen.random_greedy(16, 0.4, 5))
+    s.ensure_workspace(p)
+    f = torch.arange(2 * p, dtype=torch.int32, device="cuda")
+    acc = torch.zeros(p, dtype=torch.int32, device="cuda")
+    us = {}
+    for name, width in (("apart", 0), ("chain", 1)):
+        D = torch.from_numpy(_chain(2 * p, width)).cuda()
+        best = float("inf")
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            P.plse_stage_select(s.h, p, 2, 9, f, D, acc)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        us[name] = 1e3 * best
+    print(f"[gpu-case] select apart {us['apart']:.0f} us, chain {us['chain']:.0f} us", flush=True)
+    assert us["chain"] < 12 * us["apart"]
