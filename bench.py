@@ -43,7 +43,7 @@ sys.path.insert(0, ROOT)
 import hashlib
 
 HBM_PEAK_GBS = 8000.0
-# int32 VALU: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one operation per lane
+# int32 VALU, nominal: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz, one operation per lane
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 PLITS_SOURCES = ["k_plits.hip", "device_common.h", "kernels.h", "plse_internal.h"]
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "plits_n50_hbm.txt")

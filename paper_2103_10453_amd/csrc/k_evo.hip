@@ -162,9 +162,11 @@ struct Columns {
 // one; D[row][column] and its mirror are both written.
 //
 // Bound by the VALU: 32768 rows of n = 50, half prefilled (40 words of 6
-// planes), take 3.6 ms: the 7 operations of every pair and word run at 41 T/s, one
-// instruction a SIMD every four cycles.  Tiles of 64 x 64 staged through LDS,
-// 4 x 4 pairs a thread, took 5.06 ms (1024 rows: 70 us more).
+// planes), take 3.6 ms: the 7 operations of every pair and word run at 41 T/s.  (One
+// instruction a SIMD every four cycles of 2.4 GHz is 39.3; loops of independent
+// operations on this card run v_bitop3 and v_bcnt at 33 T/s, v_add at 55.)  Tiles
+// of 64 x 64 staged through LDS, 4 x 4 pairs a thread, took 5.06 ms (1024 rows: 70
+// us more).
 template <int B, int R>
 __global__ __launch_bounds__(256) void dist_kernel(const ArgList L) {
     const DistArgs a = arg_of<DistArgs>(L);
