@@ -186,15 +186,16 @@ int max_lds_per_block() { return g_lds_limit; }
 // modelled work of an iteration.  Its eligible vertices, 8 + |V| / 8 (6 to 22 at
 // orders 8 to 30, 24 of 1250 at n = 50, half prefilled, 145 of 1470 at n = 70,
 // 70 %), have at least `least` chunks, and a pass of them costs CH moves plus 3
-// of their like for a chunk's fixed part.
-int cheapest_chunk(const plse_instance *h, double least) {
+// of their like for a chunk's fixed part (`two` in all for CH = 2).
+int cheapest_chunk(const plse_instance *h, double least, double two) {
     int pick = 4;
     double best = 0.0;
     for (int ch : {2, 4, 8}) {
         double chunks = 0.0;
         for (int v = 0; v < h->nv; ++v) chunks += (double)((((h->vinfo[v] >> 16) & 0xFFu) + ch) / ch);
         const double per_vertex = h->nv ? chunks / h->nv : 0.0;
-        const double cost = std::max(least, (8.0 + h->nv / 8.0) * per_vertex) * (ch + 3.0);
+        const double cost = std::max(least, (8.0 + h->nv / 8.0) * per_vertex) *
+                            (ch == 2 ? two : ch + 3.0);
         if (ch == 2 || cost < best) {
             best = cost;
             pick = ch;
@@ -209,8 +210,9 @@ int cheapest_chunk(const plse_instance *h, double least) {
 // n = 30 on few passes of 8 are better (n = 70, 70 %: 2.7 ns an iteration over
 // the device with 8, 3.3 with 4), except where domains are small (n = 70, 80 %,
 // PartialCol: 1.67 with 4, 1.96 with 8; n = 90, 80 %, 60 iterations from the
-// initial population: 4 takes 1.59 ms, 8 1.76).
-int table_chunk(const plse_instance *h) { return cheapest_chunk(h, 64.0); }
+// initial population: 4 takes 1.59 ms, 8 1.76).  Chunks of 2 cost more than 2 + 3:
+// n = 28, 70 %, 4096 searches of 1200 iterations: 4 takes 4.00 ms, 2 4.16.
+int table_chunk(const plse_instance *h) { return cheapest_chunk(h, 64.0, 5.35); }
 
 // The LDS-resident kernel deals every iteration and keeps 16 waves of chunks of 2
 // or 4 a CU to 12 of chunks of 8.  4096 searches of 1200 iterations, ms, chunks of
@@ -219,7 +221,7 @@ int table_chunk(const plse_instance *h) { return cheapest_chunk(h, 64.0); }
 // 11.7; n = 90, 80 %: 65 | 59 | 69.  256 of 2500: n = 16, 40 %: 5.4 | 5.7 | 6.3.
 int lean_chunk(const plse_instance *h) {
     if (h->nv <= 128) return 2;
-    const int ch = cheapest_chunk(h, 0.0);
+    const int ch = cheapest_chunk(h, 0.0, 5.0);
     return h->nv <= 352 ? std::min(ch, 4) : ch;
 }
 

@@ -43,6 +43,7 @@ def test_lds_resident_kernel(n, ratio, size):
     (50, 0.5, 8),
     (70, 0.7, 8),
     (70, 0.8, 4),
+    (28, 0.7, 4),   # 3996, 2: 4157
     (40, 0.7, 4),   # 4743, 8: 5173
     (80, 0.8, 4),   # depth 60: 1486, 8: 1618
     (90, 0.8, 4),   # depth 60: 1590, 8: 1762
