@@ -864,9 +864,13 @@ __device__ void run_phase(const PlitsArgs &a, int64_t iters, uint32_t slot,
                 }
                 uint32_t id, pay;
                 const uint32_t any = choose(b, id, pay);
-                deal = max(deal - 1u, (1u ^ any) & nonzero((uint32_t)sc.nC) ? kCalm : 0u);
-                if (any) (void)apply(std::false_type{}, id, pay);
-                ucnt.idle += 1u ^ any;
+                --deal;
+                if (any) {
+                    (void)apply(std::false_type{}, id, pay);
+                } else {
+                    ucnt.idle++;
+                    if (PH != 3 && sc.nC != 0) deal = kCalm;  // (no conflicts in PartialCol)
+                }
                 ++itu;
                 done = itu >= end || eligible() == 0u;  // none: complete legal colouring
                 if (chunks + 32u > 64u * (uint32_t)R) deal = max(deal, 1u);
